@@ -17,13 +17,13 @@
 //   a3  the rearrangement of Algorithm 1 is never materialised: block S(i,j)
 //       of S is row i*p + j of R in address arithmetic only.
 //   a4  A_0 = block sums of S / q^2 (Sec. 4, Eqs. (18)-(19)).
-//   a5  LR-Kron (Algorithm 2) on the LDS-resident S: one sweep over S per
-//       iteration computes the residual of the previous iterate, the new time
-//       factor b = R^T conj(a) / ||a||^2 and the partial sums of R conj(b).
+//   a5  LR-Kron (Algorithm 2) on the Hermitian half of S, held in registers
+//       (Slots): per iteration the residual of the previous iterate, the new
+//       time factor b = R^T conj(a) / ||a||^2 and the sums R conj(b).
 //       EIG_{r_a} (Eq. (17)): power iteration for r_a = 1, subspace
 //       iteration otherwise, warm-started from the previous iterate.
-//   a6  final b = R^T conj(a) / ||a||^2 and its Hermitian part are queued
-//       in registers; every 64/q' pixels (q' = q rounded up to 8, 16 or 32)
+//   a6  the final b = R^T conj(a) / ||a||^2 (Hermitian) is queued in
+//       registers; every 64/q' pixels (q' = q rounded up to 8, 16 or 32)
 //       one batched subspace iteration finds the top-r_b subspaces, q' lanes
 //       per pixel with group-local DPP reductions (CGS2, residual stop).
 //   a8  T = ||F_A X conj(F_B b_s)||^2 / (b_s^H F_B b_s) (Sec. 5, Eq. (25);
@@ -513,6 +513,77 @@ __device__ __forceinline__ void power_top(MF M, C (&u)[P], bool cold, int max_st
   }
 }
 
+// Hermitian P x P matrices as P*P reals: the diagonal, then (Re, Im) of each
+// entry (i, j), i < j, at hoff(i, j).
+template <int P>
+__host__ __device__ constexpr int hoff(int i, int j) { return P + 2 * (i * P - i * (i + 1) / 2 + (j - i - 1)); }
+
+// power_top for a matrix given by its P*P reals (half the multiplications of
+// the general complex product); *lam receives u^H M u of the last iterate
+// tested, whose error is the square of the stopping residual.
+template <int P, typename C, typename S>
+__device__ __forceinline__ void power_top_h(const S (&h)[P * P], C (&u)[P], bool cold, int max_steps, double tol,
+                                            S* lam_out) {
+  if (cold) {   // the column of the largest diagonal entry
+    int jb = 0;
+    S db = h[0];
+#pragma unroll
+    for (int j = 1; j < P; ++j)
+      if (h[j] > db) {
+        db = h[j];
+        jb = j;
+      }
+    S nn = 0;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      C s = czero<C>();
+#pragma unroll
+      for (int j = 0; j < P; ++j) {
+        if (j != jb) continue;
+        if (j == i) s.x = h[i];
+        else if (i < j) s.x = h[hoff<P>(i, j)], s.y = h[hoff<P>(i, j) + 1];
+        else s.x = h[hoff<P>(j, i)], s.y = -h[hoff<P>(j, i) + 1];
+      }
+      u[i] = s;
+      nn += cabs2(s);
+    }
+    const S inv = nn > S(0) ? xrsqrt(xmax(nn, tiny<S>())) : S(0);
+#pragma unroll
+    for (int i = 0; i < P; ++i) u[i] = cscale(u[i], inv);
+  }
+  S lam = 0;
+  for (int step = 0; step < max_steps; ++step) {
+    C w[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i) w[i] = cscale(u[i], h[i]);
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+#pragma unroll
+      for (int j = i + 1; j < P; ++j) {
+        C m;
+        m.x = h[hoff<P>(i, j)];
+        m.y = h[hoff<P>(i, j) + 1];
+        w[i] = cfma(m, u[j], w[i]);
+        w[j] = ccfma(m, u[i], w[j]);
+      }
+    S wn = 0, rn = 0;
+    lam = 0;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      lam += u[i].x * w[i].x + u[i].y * w[i].y;
+      wn += cabs2(w[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < P; ++i) rn += cabs2(csub(w[i], cscale(u[i], lam)));
+    if (!(wn > S(0))) break;
+    const S inv = xrsqrt(xmax(wn, tiny<S>()));
+#pragma unroll
+    for (int i = 0; i < P; ++i) u[i] = cscale(w[i], inv);
+    if (rn <= S(tol * tol) * wn) break;
+  }
+  *lam_out = lam;
+}
+
 // Training-vector load.  Lanes whose element does not exist (rows past p*q,
 // vectors past n) read a zero from kZeroVec instead of taking a branch, so
 // every load is issued unconditionally and its value is used as loaded.
@@ -565,34 +636,6 @@ __device__ __forceinline__ void sput(float2* sS, int a, int b, float2 v) {
   const int ba = a / Q, ka = a - ba * Q, bb = b / Q, kb = b - bb * Q;
   sS[sblk<P, Q>(ba, bb) + ka * (Q + 1) + kb] = v;
   if (ba == bb) sS[sblk<P, Q>(ba, bb) + kb * (Q + 1) + ka] = make_float2(v.x, -v.y);
-}
-
-// Block sums of S and the lane's part of ||S||_F^2, gathered while S is
-// stored (for q a multiple of 16, where every 16 x 16 tile lies in one q x q
-// block): a0[i*P + j] = sum_kl S(i,j)_kl for i <= j (a lower block's sum is
-// the conjugate), each element counted with its mirror.
-template <int P>
-struct SSums {
-  float2 a0[P * P];
-  float nr;
-};
-// off: the element is not on the diagonal of S.
-template <int P, int Q>
-__device__ __forceinline__ void ssums_add(SSums<P>& ss, int I, int J, bool off, float2 v) {
-  if constexpr (Q % 16 == 0) {
-    const int bi = (16 * I) / Q, bj = (16 * J) / Q;   // constants once the tile loops unroll
-    const float m = cabs2(v);
-    if (bi != bj) {
-      ss.a0[bi * P + bj] = cadd(ss.a0[bi * P + bj], v);
-      ss.nr += 2.f * m;
-    } else if (off) {
-      ss.a0[bi * P + bi].x += 2.f * v.x;   // v + conj(v)
-      ss.nr += 2.f * m;
-    } else {
-      ss.a0[bi * P + bi] = cadd(ss.a0[bi * P + bi], v);
-      ss.nr += m;
-    }
-  }
 }
 
 // Element (tr, tc) of the 16 x 16 MFMA tile (I, J), I <= J: row 16 I + tr,
@@ -649,7 +692,7 @@ constexpr bool kOpaqueStore = Q % 16 == 0 || (P == 3 && Q == 12) || (P == 4 && Q
 template <int P, int Q>
 __device__ __forceinline__ void scm_fp32(const float2* xwin, int64_t plane, uint32_t rec, const uint32_t* sOffB,
                                          const uint32_t (&loff)[(P * Q + 15) / 16], int n, float2* sS,
-                                         float* sP, SSums<P>& ss) {
+                                         float* sP) {
   constexpr int PQ = P * Q;
   constexpr int NB = (PQ + 15) / 16;
   constexpr int NT = NB * (NB + 1) / 2;
@@ -766,7 +809,6 @@ __device__ __forceinline__ void scm_fp32(const float2* xwin, int64_t plane, uint
               const float im = (J > I) ? accI[u][q4] * inv_n
                                        : (accD[I][q4] - sP[(I * 16 + tcol) * 16 + tr]) * inv_n;
               tile_put<P, Q>(sS, I, J, tr, tcol, make_float2(re, im));
-              ssums_add<P, Q>(ss, I, J, I != J || tr != tcol, make_float2(re, im));
             }
           }
           if (J > I) ++u;
@@ -789,8 +831,7 @@ __device__ __forceinline__ void scm_fp32(const float2* xwin, int64_t plane, uint
 template <int P, int Q>
 __device__ __forceinline__ void scm_fp32_delta(const float2* xwin, int64_t plane, uint32_t rec,
                                                const uint32_t* sAdd, int nadd, const uint32_t* sRem, int nrem,
-                                               const uint32_t (&loff)[(P * Q + 15) / 16], int n, float2* sS,
-                                               SSums<P>& ss) {
+                                               const uint32_t (&loff)[(P * Q + 15) / 16], int n, float2* sS) {
   constexpr int PQ = P * Q;
   constexpr int NB = (PQ + 15) / 16;
   constexpr int NT = NB * (NB + 1) / 2;
@@ -923,7 +964,6 @@ __device__ __forceinline__ void scm_fp32_delta(const float2* xwin, int64_t plane
               v = make_float2(accR[t][q4] * inv_n, ((J > I) ? accI[u][q4] : accD[I][q4]) * inv_n);
             }
             tile_put<P, Q>(sS, I, J, tr, tcol, v);
-            ssums_add<P, Q>(ss, I, J, I != J || tr != tcol, v);
           }
         }
         if (J > I) ++u;
@@ -979,7 +1019,7 @@ __device__ __forceinline__ uint32_t hi_halves(uint32_t a, uint32_t b) { return _
 template <int P, int Q>
 __device__ __forceinline__ void scm_bf16x3(const uint32_t* hwin, const uint32_t* lwin, int64_t plane, uint32_t rec,
                                            const uint32_t* sOffB, const uint32_t (&loff)[(P * Q + 15) / 16], int n,
-                                           float2* sS, SSums<P>& ss) {
+                                           float2* sS) {
   constexpr int PQ = P * Q;
   constexpr int NB = (PQ + 15) / 16;
   constexpr int NT = NB * (NB + 1) / 2;
@@ -1076,7 +1116,6 @@ __device__ __forceinline__ void scm_bf16x3(const uint32_t* hwin, const uint32_t*
         if (tile_keep<P, Q>(I, J, tr, tcol)) {
           const float2 v = make_float2(accR[t][q4] * inv_n, accI[t][q4] * inv_n);
           tile_put<P, Q>(sS, I, J, tr, tcol, v);
-          ssums_add<P, Q>(ss, I, J, I != J || tr != tcol, v);
         }
       }
   wave_sync();
@@ -1342,6 +1381,35 @@ __device__ __forceinline__ void tail_batch(const KParams& prm, const float2 (&Bq
 // PREC 1: split-BF16 covariance, FP64 eigensolves and statistic.
 // PREC 2: FP32 covariance (full sums, no sliding window), FP64 eigensolves
 //         and statistic.
+// Hermitian slots.  S is Hermitian and so is every iterate of LR-Kron: A
+// because EIG_{r_a} returns U Hs U^H, and with it b = R^T conj(a), whose q x q
+// matrix is sum_ij conj(A_ij) S(i,j) with S(j,i) = S(i,j)^H.  The narrow
+// kernels therefore work on the q^2 real dimensions of b as q^2 / 2 slots of
+// two values: slot (k, l), l = k + d mod q, holds the complex entry B_kl (its
+// mirror B_lk is the conjugate, weight w = 2), and q / 2 slots hold two
+// diagonal entries (B_kk, B_ll), l = k + q / 2 (weight 1).  Against a slot's b
+// the P^2 blocks of R become P^2 rows of two values with real coefficients:
+//   D_i = S(i,i)_kl,  U_ij = S(i,j)_kl + conj(S(i,j)_lk),
+//   V_ij = -j (S(i,j)_kl - conj(S(i,j)_lk)),  i < j,
+//   B_kl = sum_i A_ii D_i + sum_{i<j} (Re A_ij U_ij + Im A_ij V_ij),
+//   R conj(b): A_ii = sum w D_i . b,  (Re, Im) A_ij = sum w/2 (U, V)_ij . b,
+//   ||R||^2 = sum w (|D|^2 + (|U|^2 + |V|^2) / 2).
+// One half of the products of the full q^2 x p^2 sweep, no conjugates, and
+// the values (36 registers for p = 3, q = 16) are read from LDS once per pixel
+// instead of once per sweep.  The kernels are bound by VALU issue, so this is
+// what counts: sweeps over all p^2 q^2 entries took the 2048 x 2048, p = 3,
+// q = 16, n = 200 frame 41.4 ms (FP32), the slots 32.9 ms; split BF16 at
+// 1024 x 1024 15.15 -> 13.11 ms, FP32 with FP64 solves at 512 x 512 6.50 ->
+// 5.87 ms.
+template <int P, int Q>
+struct Slots {
+  static_assert(Q % 2 == 0, "the slots pair the diagonal entries of b");
+  static constexpr int NS = Q * Q / 2;
+  // q = 8 has 32 slots: the two values of a slot go to lanes l and l + 32
+  static constexpr int C = NS <= 32 ? 1 : 2;        // values of a slot per lane
+  static constexpr int N = (NS * (2 / C) + 63) / 64;   // slots per lane
+};
+
 // LDS carve-out of one pixel pipeline (one workgroup), largest alignment first.
 template <int P, int Q, int RBM, int PREC>
 struct Lds {
@@ -1350,9 +1418,9 @@ struct Lds {
   static constexpr int RAM = (P < kMaxRA) ? P : kMaxRA;
   static constexpr int G = Groups<Q>::G;
   static constexpr int NB = (PQ + 15) / 16;
-  // B / tail / transpose scratch: the raw time factor B (q x q), the batched
-  // tail's basis exchange, and the FP32 path's diagonal-tile transpose
-  static constexpr size_t kB = sizeof(float2) * Q * Q;
+  // B / tail / transpose scratch: the time factor B (q rows of q + 2), the
+  // batched tail's basis exchange, and the FP32 path's diagonal-tile transpose
+  static constexpr size_t kB = sizeof(float2) * Q * (Q + 2);
   static constexpr size_t kT = sizeof(EC) * RBM * Q * G;
   static constexpr size_t kP = PREC == 1 ? 0 : sizeof(float) * NB * 256;
   static constexpr size_t kBT = kB > kT ? (kB > kP ? kB : kP) : (kT > kP ? kT : kP);
@@ -1381,14 +1449,14 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
   using L = Lds<P, Q, RBM, PREC>;
   constexpr int PQ = P * Q;
   constexpr int NB = (PQ + 15) / 16;        // 16-row blocks of the pq x pq covariance
-  constexpr int QQ = Q * Q;
-  constexpr int NE = (QQ + 63) / 64;        // q x q entries per lane
+  using SL = Slots<P, Q>;
+  constexpr int NS = SL::NS, NSL = SL::N, C = SL::C;
   constexpr int RAM = L::RAM;
   constexpr int QP = Groups<Q>::QP;         // lanes per pixel in the batched tail
   constexpr int G = Groups<Q>::G;           // pixels per batched tail
 
   float2* const sS = reinterpret_cast<float2*>(lds + L::oS);     // S, upper blocks
-  float2* const sBT = reinterpret_cast<float2*>(lds + L::oBT);   // raw B, then tail scratch
+  float2* const sBT = reinterpret_cast<float2*>(lds + L::oBT);   // B, then tail scratch
   uint32_t* const sOffB = reinterpret_cast<uint32_t*>(lds + L::oOff);
   // sliding window: per move, the entering then the leaving vectors
   uint32_t* const sDelta = reinterpret_cast<uint32_t*>(lds + L::oDelta);
@@ -1478,6 +1546,26 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
     }
   };
 
+  // this lane's slots: entry (sk, sl) of b, the offsets of S(i,j)_kl and
+  // S(i,j)_lk inside an upper block, and whether the last slot is a diagonal one
+  int sk[NSL], sl[NSL], so1[NSL], so2[NSL];
+  bool diag = false;
+  const int comp = (C == 1) ? lane >> 5 : 0;
+#pragma unroll
+  for (int t = 0; t < NSL; ++t) {
+    int s = (C == 1) ? (lane & 31) : lane + 64 * t;
+    if (s >= NS) s = 0;
+    const int d = s / Q + 1, k = s - (d - 1) * Q;
+    const bool dg = d == Q / 2 && k >= Q / 2;
+    sk[t] = dg ? k - Q / 2 : k;
+    sl[t] = dg ? k : (k + d) % Q;
+    so1[t] = dg ? sk[t] * (Q + 1) + sk[t] : sk[t] * (Q + 1) + sl[t];
+    so2[t] = dg ? sl[t] * (Q + 1) + sl[t] : sl[t] * (Q + 1) + sk[t];
+    if (t == NSL - 1) diag = dg;
+  }
+  // weight of a slot in sums over the entries of b
+  auto wgt = [&](int t) __attribute__((always_inline)) -> float { return (t == NSL - 1 && diag) ? 1.f : 2.f; };
+
   // Sliding window (run mode, FP32 path): every position of a chain but the
   // first is a one-pixel move from the one before it (tiled_move); such a
   // pixel updates the previous pixel's S when this workgroup has just
@@ -1485,7 +1573,10 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
   // and runs start on a chain, so the choice is the same for every
   // decomposition.
   bool chain = false;
-  bool ua_ok = false;   // sUA holds the U_A of the pixel processed last
+  bool ua_ok = false;   // ua (r_a = 1) or sUA holds the U_A of the pixel processed last
+  EC ua[P];
+#pragma unroll
+  for (int i = 0; i < P; ++i) ua[i] = czero<EC>();
   for (int64_t it = 0; it < count; ++it) {
     int64_t idx;
     int r, c;
@@ -1525,106 +1616,134 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
     // MFMAs, so they always take the full sum: no sliding-window residue)
     const int mv = tiled_move(first + it, H, W, kChainNarrow);
     const bool slide = PREC == 0 && MODE == kModeRun && left_ok && mv >= 0 && prm.nadd[0] >= 0;
-    // q a multiple of 16: the block sums and ||S||^2 of a4 are gathered while
-    // S is stored
-    constexpr bool kSums = Q % 16 == 0;
-    SSums<P> ss;
-#pragma unroll
-    for (int e = 0; e < P * P; ++e) ss.a0[e] = cz();
-    ss.nr = 0.f;
     if constexpr (PREC != 1) {
       if (slide)
         scm_fp32_delta<P, Q>(prm.x + win, plane, prm.rec_bytes, sDelta + 2 * mv * KD, prm.nadd[mv],
-                             sDelta + (2 * mv + 1) * KD, prm.nrem[mv], loff, n, sS, ss);
+                             sDelta + (2 * mv + 1) * KD, prm.nrem[mv], loff, n, sS);
       else
-        scm_fp32<P, Q>(prm.x + win, plane, prm.rec_bytes, sOffB, loff, n, sS, reinterpret_cast<float*>(sBT), ss);
+        scm_fp32<P, Q>(prm.x + win, plane, prm.rec_bytes, sOffB, loff, n, sS, reinterpret_cast<float*>(sBT));
     } else {
-      scm_bf16x3<P, Q>(prm.xs + win, prm.xs + P * plane + win, plane, prm.rec_bytes / 2, sOffB, loff, n, sS, ss);
+      scm_bf16x3<P, Q>(prm.xs + win, prm.xs + P * plane + win, plane, prm.rec_bytes / 2, sOffB, loff, n, sS);
     }
 
+    // -------------------------------------- this pixel's slots, from S in LDS
+    float v[NSL][P * P][C];
+#pragma unroll
+    for (int t = 0; t < NSL; ++t) {
+      const bool last = t == NSL - 1;   // the diagonal slots are a lane's last
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        const float2 s1 = sS[sblk<P, Q>(i, i) + so1[t]];
+        float y = s1.y;
+        if (last) {
+          const float2 s2 = sS[sblk<P, Q>(i, i) + so2[t]];
+          y = diag ? s2.x : y;
+        }
+        if constexpr (C == 2) {
+          v[t][i][0] = s1.x;
+          v[t][i][1] = y;
+        } else {
+          v[t][i][0] = comp ? y : s1.x;
+        }
+#pragma unroll
+        for (int j = i + 1; j < P; ++j) {
+          const float2 s = sS[sblk<P, Q>(i, j) + so1[t]], u = sS[sblk<P, Q>(i, j) + so2[t]];
+          float ux = s.x + u.x, uy = s.y - u.y, vx = s.y + u.y, vy = u.x - s.x;
+          if (last) {
+            ux = diag ? 2.f * s.x : ux;
+            uy = diag ? 2.f * u.x : uy;
+            vx = diag ? 2.f * s.y : vx;
+            vy = diag ? 2.f * u.y : vy;
+          }
+          if constexpr (C == 2) {
+            v[t][hoff<P>(i, j)][0] = ux;
+            v[t][hoff<P>(i, j)][1] = uy;
+            v[t][hoff<P>(i, j) + 1][0] = vx;
+            v[t][hoff<P>(i, j) + 1][1] = vy;
+          } else {
+            v[t][hoff<P>(i, j)][0] = comp ? uy : ux;
+            v[t][hoff<P>(i, j) + 1][0] = comp ? vy : vx;
+          }
+        }
+      }
+      if (NS % 64 != 0 && !(lane + 64 * t < NS * (2 / C))) {   // no such slot
+#pragma unroll
+        for (int e = 0; e < P * P; ++e)
+#pragma unroll
+          for (int c2 = 0; c2 < C; ++c2) v[t][e][c2] = 0.f;
+      }
+    }
+
+    // R conj(b), given w b, as uniform values (P*P reals); `extra` is summed with it
+    auto half_a = [&](const float (&wb)[NSL][C], float (&out)[P * P], float& extra) __attribute__((always_inline)) {
+      constexpr int NR = (P * P + 1 + 3) / 4 * 4;
+      float sums[NR];
+#pragma unroll
+      for (int e = 0; e < NR; ++e) sums[e] = (e == P * P) ? extra : 0.f;
+#pragma unroll
+      for (int t = 0; t < NSL; ++t)
+#pragma unroll
+        for (int c2 = 0; c2 < C; ++c2)
+#pragma unroll
+          for (int e = 0; e < P * P; ++e) sums[e] = fmaf(v[t][e][c2], wb[t][c2], sums[e]);
+      wsum_n<NR>(sums);
+#pragma unroll
+      for (int e = 0; e < P * P; ++e) out[e] = (e < P) ? sums[e] : 0.5f * sums[e];
+      extra = sums[P * P];
+    };
+
     // ------------------------------------------------ a4 init, ||R||_F = ||S||_F
-    float2 A[P * P];
+    float A[P * P];   // the space factor A as P*P reals (hoff)
+    float anorm2;
+    auto norm_a = [&]() __attribute__((always_inline)) {
+      anorm2 = 0.f;
+#pragma unroll
+      for (int e = 0; e < P; ++e) anorm2 = fmaf(A[e], A[e], anorm2);
+      float o = 0.f;
+#pragma unroll
+      for (int e = P; e < P * P; ++e) o = fmaf(A[e], A[e], o);
+      anorm2 = fmaf(2.f, o, anorm2);
+    };
     double normR2;
     {
-      float2 a0[P * P];
-      if constexpr (kSums) {
-        normR2 = wsumd(double(ss.nr));
-        // the upper block sums in one multi-value reduction
-        constexpr int NU = P * (P + 1) / 2, NS = (2 * NU + 3) / 4 * 4;
-        float sums[NS];
-        {
-          int e = 0;
+      float nr = 0.f;
 #pragma unroll
-          for (int i = 0; i < P; ++i)
+      for (int t = 0; t < NSL; ++t) {
+        float nd = 0.f, no = 0.f;
 #pragma unroll
-            for (int j = i; j < P; ++j, e += 2) {
-              sums[e] = ss.a0[i * P + j].x;
-              sums[e + 1] = ss.a0[i * P + j].y;
-            }
+        for (int c2 = 0; c2 < C; ++c2)
 #pragma unroll
-          for (int f = 2 * NU; f < NS; ++f) sums[f] = 0.f;
-        }
-        wsum_n<NS>(sums);
-        {
-          int e = 0;
-#pragma unroll
-          for (int i = 0; i < P; ++i)
-#pragma unroll
-            for (int j = i; j < P; ++j, e += 2) {
-              a0[i * P + j] = cscale(make_float2(sums[e], sums[e + 1]), 1.f / float(QQ));
-              if (j > i) a0[j * P + i] = cconj(a0[i * P + j]);
-            }
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < P * P; ++e) a0[e] = cz();
-        float nr = 0.f;
-#pragma unroll
-        for (int t = 0; t < NE; ++t) {
-          const int e = lane + 64 * t;
-          if (e < QQ) {
-            const int k = e / Q, l = e - (e / Q) * Q;
-#pragma unroll
-            for (int i = 0; i < P; ++i)
-#pragma unroll
-              for (int j = 0; j < P; ++j) {
-                const float2 s = sget<P, Q>(sS, i, j, k, l);
-                a0[i * P + j] = cadd(a0[i * P + j], s);
-                nr += cabs2(s);
-              }
+          for (int e = 0; e < P * P; ++e) {
+            if (e < P) nd = fmaf(v[t][e][c2], v[t][e][c2], nd);
+            else no = fmaf(v[t][e][c2], v[t][e][c2], no);
           }
-        }
-        normR2 = wsumd(double(nr));
-        constexpr int NS = (2 * P * P + 3) / 4 * 4;
-        float sums[NS];
-#pragma unroll
-        for (int f = 0; f < NS; ++f) sums[f] = (f < 2 * P * P) ? ((f & 1) ? a0[f / 2].y : a0[f / 2].x) : 0.f;
-        wsum_n<NS>(sums);
-#pragma unroll
-        for (int e = 0; e < P * P; ++e) a0[e] = cscale(make_float2(sums[2 * e], sums[2 * e + 1]), 1.f / float(QQ));
+        nr = fmaf(wgt(t), fmaf(0.5f, no, nd), nr);
       }
-      float an = 0.f;
+      normR2 = wsumd(double(nr));
+      // A_0 = R 1 / q^2 (block sums): b is the all-ones matrix, or (fallback)
+      // R vec(I_q): b is the identity
+      float wb[NSL][C], none = 0.f;
 #pragma unroll
-      for (int e = 0; e < P * P; ++e) {
-        A[e] = a0[e];
-        an += cabs2(a0[e]);
-      }
-      if (double(an) <= 1e-24 * normR2) {   // fallback: partial trace R vec(I_q) (uniform branch)
-        float2 pt[P * P];
-#pragma unroll
-        for (int e = 0; e < P * P; ++e) pt[e] = cz();
-#pragma unroll
-        for (int t = 0; t < NE; ++t) {
-          const int e = lane + 64 * t;
-          if (e < QQ && e / Q == e - (e / Q) * Q) {
-#pragma unroll
-            for (int i = 0; i < P; ++i)
-#pragma unroll
-              for (int j = 0; j < P; ++j) pt[i * P + j] = cadd(pt[i * P + j], sget<P, Q>(sS, i, j, e / Q, e / Q));
-          }
+      for (int t = 0; t < NSL; ++t) {
+        if constexpr (C == 2) {
+          wb[t][0] = wgt(t);
+          wb[t][1] = (t == NSL - 1 && diag) ? 1.f : 0.f;
+        } else {
+          wb[t][0] = (comp && !diag) ? 0.f : wgt(t);
         }
+      }
+      half_a(wb, A, none);
 #pragma unroll
-        for (int e = 0; e < P * P; ++e) A[e] = wsum(pt[e]);
+      for (int e = 0; e < P * P; ++e) A[e] *= 1.f / float(Q * Q);
+      norm_a();
+      if (double(anorm2) <= 1e-24 * normR2) {   // uniform branch
+#pragma unroll
+        for (int t = 0; t < NSL; ++t)
+#pragma unroll
+          for (int c2 = 0; c2 < C; ++c2) wb[t][c2] = (t == NSL - 1 && diag) ? 1.f : 0.f;
+        none = 0.f;
+        half_a(wb, A, none);
+        norm_a();
       }
     }
 
@@ -1633,72 +1752,62 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
     const bool zero = !(normR2 > 0.0);
     const bool bad = !isfinite(normR2);
     chain = !bad;   // this S may seed the next pixel's
-    float2 bv[NE];
+    float bv[NSL][C];
 #pragma unroll
-    for (int t = 0; t < NE; ++t) bv[t] = cz();
+    for (int t = 0; t < NSL; ++t)
+#pragma unroll
+      for (int c2 = 0; c2 < C; ++c2) bv[t][c2] = 0.f;
 
     if (!zero && !bad) {
       // --------------------------------------------------------- a5 LR-Kron
-      float2 Ap[P * P];
-      float bn2;
-      double resid = 0.0;
-      float anorm2 = 0.f;
-#pragma unroll
-      for (int e = 0; e < P * P; ++e) anorm2 += cabs2(A[e]);
+      float Ap[P * P];   // A' = R conj(b) / ||b||^2, P*P reals
 
-      // one sweep over S: residual of (A, bv) if RES, then the new b and the
-      // partial sums of R conj(b)
-      auto sweep = [&](bool res) __attribute__((always_inline)) {
+      // b = R^T conj(a) / ||a||^2
+      auto half_b = [&]() __attribute__((always_inline)) {
         const float ainv = xrcp(anorm2);
-        float2 ap[P * P];
 #pragma unroll
-        for (int e = 0; e < P * P; ++e) ap[e] = cz();
-        float bb = 0.f;
+        for (int t = 0; t < NSL; ++t)
+#pragma unroll
+          for (int c2 = 0; c2 < C; ++c2) {
+            float s = 0.f;
+#pragma unroll
+            for (int e = 0; e < P * P; ++e) s = fmaf(A[e], v[t][e][c2], s);
+            bv[t][c2] = s * ainv;
+          }
+      };
+      // ||R - a b^T||_F^2: per entry in FP32, summed over the lanes in FP64
+      auto residual = [&]() __attribute__((always_inline)) -> double {
         double rr = 0.0;
 #pragma unroll
-        for (int t = 0; t < NE; ++t) {
-          const int e = lane + 64 * t;
-          if (QQ % 64 == 0 || e < QQ) {
-            const int k = e / Q, l = e - (e / Q) * Q;
-            float2 s[P * P];
+        for (int t = 0; t < NSL; ++t) {
+          float rd = 0.f, ro = 0.f;
 #pragma unroll
-            for (int i = 0; i < P; ++i)
+          for (int c2 = 0; c2 < C; ++c2)
 #pragma unroll
-              for (int j = 0; j < P; ++j) s[i * P + j] = sget<P, Q>(sS, i, j, k, l);
-            if (res) {
-              float acc = 0.f;
-#pragma unroll
-              for (int ij = 0; ij < P * P; ++ij) acc += cabs2(csub(s[ij], cmul(A[ij], bv[t])));
-              rr += double(acc);
+            for (int e = 0; e < P * P; ++e) {
+              const float m = (e < P) ? A[e] : 2.f * A[e];
+              const float d = fmaf(-m, bv[t][c2], v[t][e][c2]);
+              if (e < P) rd = fmaf(d, d, rd);
+              else ro = fmaf(d, d, ro);
             }
-            float2 bn = cz();
+          rr += double(wgt(t) * fmaf(0.5f, ro, rd));
+        }
+        return wsumd(rr);
+      };
+      // A' and the sum ||b||^2 from the current b
+      auto half_ap = [&]() __attribute__((always_inline)) {
+        float wb[NSL][C], bn2 = 0.f;
 #pragma unroll
-            for (int ij = 0; ij < P * P; ++ij) bn = ccfma(A[ij], s[ij], bn);
-            bn = cscale(bn, ainv);
-            bv[t] = bn;
-            bb += cabs2(bn);
+        for (int t = 0; t < NSL; ++t)
 #pragma unroll
-            for (int ij = 0; ij < P * P; ++ij) ap[ij] = ccfma(bn, s[ij], ap[ij]);
-          } else {
-            bv[t] = cz();
+          for (int c2 = 0; c2 < C; ++c2) {
+            wb[t][c2] = wgt(t) * bv[t][c2];
+            bn2 = fmaf(wb[t][c2], bv[t][c2], bn2);
           }
-        }
-        // the 2 p^2 sums of R conj(b) and ||b||^2 in one multi-value reduction
-        constexpr int NS = (2 * P * P + 1 + 3) / 4 * 4;
-        float sums[NS];
-#pragma unroll
-        for (int ij = 0; ij < P * P; ++ij) {
-          sums[2 * ij] = ap[ij].x;
-          sums[2 * ij + 1] = ap[ij].y;
-        }
-#pragma unroll
-        for (int e = 2 * P * P; e < NS; ++e) sums[e] = (e == 2 * P * P) ? bb : 0.f;
-        wsum_n<NS>(sums);
-        bn2 = sums[2 * P * P];
+        half_a(wb, Ap, bn2);
         const float binv = xrcp(bn2);
 #pragma unroll
-        for (int ij = 0; ij < P * P; ++ij) Ap[ij] = cscale(make_float2(sums[2 * ij], sums[2 * ij + 1]), binv);
-        if (res) resid = wsumd(rr);
+        for (int e = 0; e < P * P; ++e) Ap[e] *= binv;
       };
 
       // EIG_{r_a}: A <- U (U^H A' U) U^H with U the top-r_a subspace of Herm(A').
@@ -1706,42 +1815,34 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
       // U_A (sUA): the two training sets differ in a few vectors.  The choice
       // depends only on the chain position, as the sliding window does.
       const bool warm = slide && ua_ok;
-      EC ua[P];
-#pragma unroll
-      for (int i = 0; i < P; ++i) ua[i] = warm ? sUA[i * RAM] : czero<EC>();
       auto eig_a = [&](bool cold) __attribute__((always_inline)) {
-        EC Ah[P * P];
-#pragma unroll
-        for (int i = 0; i < P; ++i)
-#pragma unroll
-          for (int j = 0; j < P; ++j)
-            Ah[i * P + j] = cscale(cadd(cto<EC>(Ap[i * P + j]), cconj(cto<EC>(Ap[j * P + i]))), ES(0.5));
         if (r_a == 1) {
-          power_top<P, EC>([&](int i, int j) { return Ah[i * P + j]; }, ua, cold, 500, PREC ? 1e-12 : 2e-6);
-          ES lam = 0;
+          ES h[P * P], lam;
+#pragma unroll
+          for (int e = 0; e < P * P; ++e) h[e] = ES(Ap[e]);
+          power_top_h<P, EC, ES>(h, ua, cold, 500, PREC ? 1e-12 : 2e-6, &lam);
 #pragma unroll
           for (int i = 0; i < P; ++i) {
-            EC s = czero<EC>();
+            A[i] = float(lam * cabs2(ua[i]));
 #pragma unroll
-            for (int j = 0; j < P; ++j) s = cfma(Ah[i * P + j], ua[j], s);
-            lam += ua[i].x * s.x + ua[i].y * s.y;
-          }
-          anorm2 = 0.f;
-#pragma unroll
-          for (int i = 0; i < P; ++i)
-#pragma unroll
-            for (int j = 0; j < P; ++j) {
-              A[i * P + j] = tof(cscale(cmul(ua[i], cconj(ua[j])), lam));
-              anorm2 += cabs2(A[i * P + j]);
+            for (int j = i + 1; j < P; ++j) {
+              const EC c2 = cmul(ua[i], cconj(ua[j]));
+              A[hoff<P>(i, j)] = float(lam * c2.x);
+              A[hoff<P>(i, j) + 1] = float(lam * c2.y);
             }
-          // one lane writes U_A with static indices (a lane-indexed select
-          // over ua[] is compiled into a scratch array)
-          if (lane == 0) {
-#pragma unroll
-            for (int i = 0; i < P; ++i) sUA[i * RAM] = ua[i];
           }
-          wave_sync();
+          norm_a();
           return;
+        }
+        EC Ah[P * P];
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+          Ah[i * P + i] = cto<EC>(make_float2(Ap[i], 0.f));
+#pragma unroll
+          for (int j = i + 1; j < P; ++j) {
+            Ah[i * P + j] = cto<EC>(make_float2(Ap[hoff<P>(i, j)], Ap[hoff<P>(i, j) + 1]));
+            Ah[j * P + i] = cconj(Ah[i * P + j]);
+          }
         }
         // r_a > 1: the top-r_a subspace of Herm(A'), warm-started from the
         // previous U_A (in LDS).  p <= 4: every lane runs the same subspace
@@ -1811,11 +1912,10 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
             }
             Hs[a][b] = sacc;
           }
-        anorm2 = 0.f;
 #pragma unroll
         for (int i = 0; i < P; ++i)
 #pragma unroll
-          for (int j = 0; j < P; ++j) {
+          for (int j = i; j < P; ++j) {
             EC sacc = czero<EC>();
 #pragma unroll
             for (int a = 0; a < RAM; ++a) {
@@ -1826,26 +1926,33 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
                 if (b < r_a) t2 = cfma(Hs[a][b], cconj(Vb[b][j]), t2);
               sacc = cfma(Vb[a][i], t2, sacc);
             }
-            A[i * P + j] = tof(sacc);
-            anorm2 += cabs2(A[i * P + j]);
+            if (i == j) {
+              A[i] = float(sacc.x);
+            } else {
+              A[hoff<P>(i, j)] = float(sacc.x);
+              A[hoff<P>(i, j) + 1] = float(sacc.y);
+            }
           }
+        norm_a();
         wave_sync();
       };
 
-      sweep(false);
-      eig_a(!warm);
-      iters = 1;
+      // one call site per lambda: iteration 0 has no residual yet
       double eta_prev = INFINITY;
-      while (true) {
-        sweep(true);
-        const double e = sqrt(resid / normR2);
-        eta = float(e);
-        const bool stop = iters >= prm.max_iter ||
-                          (prm.eps > 0.0 && iters >= prm.min_iter && fabs(e - eta_prev) <= prm.eps);
-        if (stop) break;
-        eta_prev = e;
-        eig_a(false);
-        ++iters;
+      for (int k = 0;; ++k) {
+        double e = 0.0;
+        if (k > 0) e = sqrt(residual() / normR2);
+        half_b();
+        if (k > 0) {
+          eta = float(e);
+          const bool stop = iters >= prm.max_iter ||
+                            (prm.eps > 0.0 && iters >= prm.min_iter && fabs(e - eta_prev) <= prm.eps);
+          if (stop) break;
+          eta_prev = e;
+        }
+        half_ap();
+        eig_a(k == 0 && !warm);
+        iters = k + 1;
       }
       // bv now holds the final b = R^T conj(a) / ||a||^2
     }
@@ -1870,15 +1977,33 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
       }
       if constexpr (kWarmTail) qchain = cid;
     }
+    // the Hermitian B from its slots, B[k][l] at k * BS + l, then one row per lane
+    constexpr int BS = Q + 2;   // 16-byte rows, spread over the banks
 #pragma unroll
-    for (int t = 0; t < NE; ++t) {
-      const int e = lane + 64 * t;
-      if (QQ % 64 == 0 || e < QQ) sBT[e] = bv[t];   // B[k][l] at k*q + l
+    for (int t = 0; t < NSL; ++t) {
+      if (NS % 64 == 0 || lane + 64 * t < NS * (2 / C)) {
+        const bool dg = t == NSL - 1 && diag;
+        const int k1 = sk[t], l1 = sl[t];
+        if constexpr (C == 2) {
+          sBT[dg ? k1 * BS + k1 : k1 * BS + l1] = make_float2(bv[t][0], dg ? 0.f : bv[t][1]);
+          sBT[dg ? l1 * BS + l1 : l1 * BS + k1] = make_float2(dg ? bv[t][1] : bv[t][0], dg ? 0.f : -bv[t][1]);
+        } else {
+          float* const f = reinterpret_cast<float*>(sBT);
+          const int kk = comp ? l1 : k1;   // the diagonal entry of this lane
+          f[dg ? 2 * (kk * BS + kk) : 2 * (k1 * BS + l1) + comp] = bv[t][0];
+          f[dg ? 2 * (kk * BS + kk) + 1 : 2 * (l1 * BS + k1) + comp] = dg ? 0.f : (comp ? -bv[t][0] : bv[t][0]);
+        }
+      }
     }
     wave_sync();
     if (tg == nq && tk < Q) {
+      const float4* const row = reinterpret_cast<const float4*>(sBT + tk * BS);
 #pragma unroll
-      for (int l = 0; l < Q; ++l) Bq[l] = cscale(cadd(sBT[tk * Q + l], cconj(sBT[l * Q + tk])), 0.5f);
+      for (int l = 0; l < Q / 2; ++l) {
+        const float4 two = row[l];
+        Bq[2 * l] = make_float2(two.x, two.y);
+        Bq[2 * l + 1] = make_float2(two.z, two.w);
+      }
     }
     if (lane == 0) {
       sQidx[nq] = idx;
@@ -1886,7 +2011,16 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
       sQeta[nq] = eta;
       sQit[nq] = iters;
     }
-    if (lane < P * RAM) sQUA[nq][lane] = (zero || bad) ? czero<EC>() : sUA[lane];
+    if (r_a == 1) {
+      // one lane writes U_A with static indices (a lane-indexed select over
+      // ua[] is compiled into a scratch array)
+      if (lane == 0) {
+#pragma unroll
+        for (int i = 0; i < P; ++i) sQUA[nq][i * RAM] = (zero || bad) ? czero<EC>() : ua[i];
+      }
+    } else if (lane < P * RAM) {
+      sQUA[nq][lane] = (zero || bad) ? czero<EC>() : sUA[lane];
+    }
     wave_sync();
     ++nq;
   }
