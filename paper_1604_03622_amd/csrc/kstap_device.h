@@ -7,10 +7,11 @@
 // the tiled pixel order.
 //
 //   a2  sample covariance S = (1/n) sum_m x_m x_m^H  (Sec. 1.1, Eq. (2)) as a
-//       dense contraction on MFMA.  FP32 path: v_mfma_f32_16x16x4_f32 with
-//       Re S = Xr Xr^T + Xi Xi^T and Im S = Xi Xr^T - Xr Xi^T over the upper
-//       16 x 16 tiles (diagonal tiles of Im S from one product and its
-//       transpose).  Mixed path: three BF16 products on pre-split planes.
+//       dense contraction on MFMA.  FP32 path: Re S = Xr Xr^T + Xi Xi^T and
+//       Im S = Xi Xr^T - Xr Xi^T over the upper 16 x 16 tiles, on the BF16
+//       pipe with every sample split exactly into three BF16 parts (scm_split;
+//       v_mfma_f32_16x16x4_f32 for p q > 48 and the Doppler bank).  Mixed
+//       path: three BF16 products on pre-split planes.
 //       Training vectors are read through buffer resources straight into
 //       MFMA operands; workgroups that are in flight together on one XCD
 //       cover a compact patch, so their windows are served from its L2.
@@ -605,6 +606,7 @@ __device__ __forceinline__ float2 load_or_zero(const float2* p, bool keep) {
 // arithmetic per load.
 constexpr uint32_t kOut = 0x80000000u;
 constexpr int kOffPad = 64;   // sOffB entries past kMaxN (prefetch overrun, all kOut)
+constexpr int kDeltaList = 2 * kMaxDelta + 32;   // a move's entering, then leaving vectors, then kOut
 
 template <int Q>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t block_rsrc(const float2* xwin, int64_t plane, uint32_t rec, int I) {
@@ -636,6 +638,34 @@ __device__ __forceinline__ void sput(float2* sS, int a, int b, float2 v) {
   const int ba = a / Q, ka = a - ba * Q, bb = b / Q, kb = b - bb * Q;
   sS[sblk<P, Q>(ba, bb) + ka * (Q + 1) + kb] = v;
   if (ba == bb) sS[sblk<P, Q>(ba, bb) + kb * (Q + 1) + ka] = make_float2(v.x, -v.y);
+}
+
+// Block sums of S and the lane's part of ||S||_F^2, gathered while S is
+// stored (for q a multiple of 16, where every 16 x 16 tile lies in one q x q
+// block): a0[i*P + j] = sum_kl S(i,j)_kl for i <= j (a lower block's sum is
+// the conjugate), each element counted with its mirror.
+template <int P>
+struct SSums {
+  float2 a0[P * P];
+  float nr;
+};
+// off: the element is not on the diagonal of S.
+template <int P, int Q>
+__device__ __forceinline__ void ssums_add(SSums<P>& ss, int I, int J, bool off, float2 v) {
+  if constexpr (Q % 16 == 0) {
+    const int bi = (16 * I) / Q, bj = (16 * J) / Q;   // constants once the tile loops unroll
+    const float m = cabs2(v);
+    if (bi != bj) {
+      ss.a0[bi * P + bj] = cadd(ss.a0[bi * P + bj], v);
+      ss.nr += 2.f * m;
+    } else if (off) {
+      ss.a0[bi * P + bi].x += 2.f * v.x;   // v + conj(v)
+      ss.nr += 2.f * m;
+    } else {
+      ss.a0[bi * P + bi] = cadd(ss.a0[bi * P + bi], v);
+      ss.nr += m;
+    }
+  }
 }
 
 // Element (tr, tc) of the 16 x 16 MFMA tile (I, J), I <= J: row 16 I + tr,
@@ -692,7 +722,7 @@ constexpr bool kOpaqueStore = Q % 16 == 0 || (P == 3 && Q == 12) || (P == 4 && Q
 template <int P, int Q>
 __device__ __forceinline__ void scm_fp32(const float2* xwin, int64_t plane, uint32_t rec, const uint32_t* sOffB,
                                          const uint32_t (&loff)[(P * Q + 15) / 16], int n, float2* sS,
-                                         float* sP) {
+                                         float* sP, SSums<P>& ss) {
   constexpr int PQ = P * Q;
   constexpr int NB = (PQ + 15) / 16;
   constexpr int NT = NB * (NB + 1) / 2;
@@ -809,6 +839,7 @@ __device__ __forceinline__ void scm_fp32(const float2* xwin, int64_t plane, uint
               const float im = (J > I) ? accI[u][q4] * inv_n
                                        : (accD[I][q4] - sP[(I * 16 + tcol) * 16 + tr]) * inv_n;
               tile_put<P, Q>(sS, I, J, tr, tcol, make_float2(re, im));
+              ssums_add<P, Q>(ss, I, J, I != J || tr != tcol, make_float2(re, im));
             }
           }
           if (J > I) ++u;
@@ -831,7 +862,8 @@ __device__ __forceinline__ void scm_fp32(const float2* xwin, int64_t plane, uint
 template <int P, int Q>
 __device__ __forceinline__ void scm_fp32_delta(const float2* xwin, int64_t plane, uint32_t rec,
                                                const uint32_t* sAdd, int nadd, const uint32_t* sRem, int nrem,
-                                               const uint32_t (&loff)[(P * Q + 15) / 16], int n, float2* sS) {
+                                               const uint32_t (&loff)[(P * Q + 15) / 16], int n, float2* sS,
+                                               SSums<P>& ss) {
   constexpr int PQ = P * Q;
   constexpr int NB = (PQ + 15) / 16;
   constexpr int NT = NB * (NB + 1) / 2;
@@ -964,12 +996,257 @@ __device__ __forceinline__ void scm_fp32_delta(const float2* xwin, int64_t plane
               v = make_float2(accR[t][q4] * inv_n, ((J > I) ? accI[u][q4] : accD[I][q4]) * inv_n);
             }
             tile_put<P, Q>(sS, I, J, tr, tcol, v);
+            ssums_add<P, Q>(ss, I, J, I != J || tr != tcol, v);
           }
         }
         if (J > I) ++u;
         ++t;
       }
   }
+  wave_sync();
+}
+
+// ------------------------------------------- a2, FP32 in three BF16 parts
+// S of FP32 samples on the BF16 matrix pipe: x = h + m + l, each part the
+// BF16 rounding of what the parts before it leave, is exact (8 + 8 + 8 bits
+// with signs), and x y ~ hh' + hm' + mh' + mm' + hl' + lh' drops products
+// below 2^-26 |x y|, a quarter of an FP32 rounding.  Every tile takes six
+// products of Re and six of Im per 16 vectors, accumulated in FP32 (six
+// roundings per 16 vectors instead of eight).  FP32 MFMA runs on the FMA
+// units, so its time adds to the VALU's (measured: one wave of each on a SIMD
+// take the sum of their times), while BF16 MFMA hides under the other
+// wavefront's VALU work (17.5 cycles per MFMA with and without FMAs beside
+// it): 72 x 16 matrix-pipe cycles per 16 vectors and three 16-row blocks, off
+// the critical path, against 4 x 18 x 32 on it.
+//   In a 16-vector chunk, lane (g = lane / 16, r = lane % 16) holds row r of
+// every block for vectors 4g .. 4g + 3, packed in pairs: a row operand is
+// (re_01, im_01, re_23, im_23).  The column operand of Re S has the same
+// order; that of Im S = im re' - re im' is (-im_01, re_01, -im_23, re_23).  A
+// leaving vector's column operands take its sign.  A remainder of up to 8
+// vectors takes a half chunk (vectors 2g, 2g + 1) on the K = 16 MFMA.
+//   S is kept as n S in the accumulators, and they stay in registers from one
+// pixel of a sliding-window chain to the next where there is room (kKeepAcc).
+// Measured against FP32 MFMA: 2048 x 2048, p = 3, q = 16, n = 200 32.9 -> 27.7
+// ms; FP32 with FP64 solves (all n vectors per pixel) 512 x 512 5.87 -> 5.08
+// ms; 187 x 233, q = 12, n = 128 627 -> 501 us; errors against FP64 the same
+// or smaller.  Classes of four 16-row blocks keep FP32 MFMA: their operands
+// and 20 accumulators do not fit beside the pixel state.
+template <int P, int Q>
+constexpr bool kSplitCov = (P * Q + 15) / 16 <= 3;
+template <int P, int Q>
+constexpr bool kKeepAcc = kSplitCov<P, Q> && P <= 4;
+
+template <int P, int Q>
+struct SplitAcc {
+  static constexpr int NB = (P * Q + 15) / 16;
+  static constexpr int NT = NB * (NB + 1) / 2;
+  f4 r[NT], i[NT];   // Re and Im of n S, tile (I, J) at I NB - I (I - 1) / 2 + J - I
+};
+
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+typedef short s4 __attribute__((ext_vector_type(4)));
+
+template <int V>
+struct VecsPerLane {
+  static constexpr int value = V;
+};
+
+// the three BF16 parts of a (low halves) and b (high halves)
+__device__ __forceinline__ void split3(float a, float b, uint32_t (&part)[3]) {
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    const f2v ab{a, b};
+    part[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(ab, bf2));
+    if (e < 2) {
+      a -= __builtin_bit_cast(float, part[e] << 16);
+      b -= __builtin_bit_cast(float, part[e] & 0xffff0000u);
+    }
+  }
+}
+
+// n S += sum over the vectors list[0 .. npos) - sum over list[npos .. cnt):
+// byte offsets in LDS, kOut past cnt for 32 entries.  PF chunks are in flight:
+// one where another wavefront fills the wait and the windows are in L2 (run
+// mode); three for the pixel lists of the probe, whose windows come from HBM
+// (no leaving vectors there).
+template <int P, int Q, int PF>
+__device__ __forceinline__ void scm_split(const float2* xwin, int64_t plane, uint32_t rec, const uint32_t* list,
+                                          int npos, int cnt, const uint32_t (&loff)[(P * Q + 15) / 16],
+                                          SplitAcc<P, Q>& acc) {
+  constexpr int NB = SplitAcc<P, Q>::NB;
+  const int g = threadIdx.x >> 4;
+  __amdgpu_buffer_rsrc_t rs[NB];
+#pragma unroll
+  for (int I = 0; I < NB; ++I) rs[I] = block_rsrc<Q>(xwin, plane, rec, I);
+  float2 ring[PF][NB][4];   // chunk ch in ring[ch % PF], refetched as soon as its vectors are split
+  auto fetch = [&](int m, float2 (&v)[NB][4]) __attribute__((always_inline)) {
+    const uint4 o = *reinterpret_cast<const uint4*>(list + m + 4 * g);
+    const uint32_t off[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int I = 0; I < NB; ++I) v[I][e] = bload(rs[I], loff[I] + off[e]);
+  };
+  auto fetch_half = [&](int m, float2 (&v)[NB][4]) __attribute__((always_inline)) {
+    const uint2 o = *reinterpret_cast<const uint2*>(list + m + 2 * g);
+    const uint32_t off[2] = {o.x, o.y};
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int I = 0; I < NB; ++I) v[I][e] = bload(rs[I], loff[I] + off[e]);
+  };
+  // MFMAs of one chunk of V vectors per lane; sign[k]: sign bits of the pair k;
+  // `then` runs once the raw samples are consumed
+  auto accumulate = [&](auto vc, const float2 (&raw)[NB][4], const uint32_t (&sign)[2], auto then)
+                        __attribute__((always_inline)) {
+    constexpr int V = decltype(vc)::value;
+    uint32_t y[NB][3][V];
+#pragma unroll
+    for (int I = 0; I < NB; ++I)
+#pragma unroll
+      for (int k = 0; k < V / 2; ++k) {
+        uint32_t re[3], im[3];
+        split3(raw[I][2 * k].x, raw[I][2 * k + 1].x, re);
+        split3(raw[I][2 * k].y, raw[I][2 * k + 1].y, im);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          y[I][e][2 * k] = re[e];
+          y[I][e][2 * k + 1] = im[e];
+        }
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    then();
+    __builtin_amdgcn_sched_barrier(0);
+    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};   // small products first
+#pragma unroll
+    for (int J = NB - 1; J >= 0; --J) {
+      uint32_t cr[3][V], ci[3][V];
+#pragma unroll
+      for (int e = 0; e < 3; ++e)
+#pragma unroll
+        for (int k = 0; k < V / 2; ++k) {
+          cr[e][2 * k] = y[J][e][2 * k] ^ sign[k];
+          cr[e][2 * k + 1] = y[J][e][2 * k + 1] ^ sign[k];
+          ci[e][2 * k] = y[J][e][2 * k + 1] ^ (sign[k] ^ 0x80008000u);
+          ci[e][2 * k + 1] = cr[e][2 * k];
+        }
+#pragma unroll
+      for (int w = 0; w < 6; ++w)
+#pragma unroll
+        for (int I = 0; I <= J; ++I) {
+          const int t = I * NB - I * (I - 1) / 2 + J - I;
+          if constexpr (V == 4) {
+            const bf8 row = __builtin_bit_cast(bf8, u4{y[I][pa[w]][0], y[I][pa[w]][1], y[I][pa[w]][2], y[I][pa[w]][3]});
+            const bf8 c0 = __builtin_bit_cast(bf8, u4{cr[pb[w]][0], cr[pb[w]][1], cr[pb[w]][2], cr[pb[w]][3]});
+            const bf8 c1 = __builtin_bit_cast(bf8, u4{ci[pb[w]][0], ci[pb[w]][1], ci[pb[w]][2], ci[pb[w]][3]});
+            acc.r[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row, c0, acc.r[t], 0, 0, 0);
+            acc.i[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row, c1, acc.i[t], 0, 0, 0);
+          } else {
+            const s4 row = __builtin_bit_cast(s4, u2{y[I][pa[w]][0], y[I][pa[w]][1]});
+            const s4 c0 = __builtin_bit_cast(s4, u2{cr[pb[w]][0], cr[pb[w]][1]});
+            const s4 c1 = __builtin_bit_cast(s4, u2{ci[pb[w]][0], ci[pb[w]][1]});
+            acc.r[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(row, c0, acc.r[t], 0, 0, 0);
+            acc.i[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(row, c1, acc.i[t], 0, 0, 0);
+          }
+        }
+    }
+  };
+  const int nfull = (cnt + 7) >> 4;          // a remainder of 9 to 15 fills a chunk (zeros past cnt)
+  const bool half = cnt > 16 * nfull;        // 1 to 8 vectors left
+  const uint32_t none[2] = {0u, 0u};
+  if constexpr (PF > 1) {
+    float2 rest[NB][4];
+    if (half) fetch_half(16 * nfull, rest);
+#pragma unroll
+    for (int sl = 0; sl < PF; ++sl)
+      if (sl < nfull) fetch(16 * sl, ring[sl]);
+#pragma unroll 1
+    for (int ch0 = 0; ch0 < nfull; ch0 += PF) {
+#pragma unroll
+      for (int sl = 0; sl < PF; ++sl)
+        if (ch0 + sl < nfull)
+          accumulate(VecsPerLane<4>(), ring[sl], none, [&]() __attribute__((always_inline)) {
+            if (ch0 + sl + PF < nfull) fetch(16 * (ch0 + sl + PF), ring[sl]);
+          });
+    }
+    if (half) accumulate(VecsPerLane<2>(), rest, none, [] {});
+    return;
+  }
+  float2(&raw)[NB][4] = ring[0];
+  if (nfull > 0) fetch(0, raw);
+  else fetch_half(0, raw);
+#pragma unroll 1
+  for (int ch = 0; ch < nfull; ++ch) {
+    auto next = [&]() __attribute__((always_inline)) {
+      if (ch + 1 < nfull) fetch(16 * (ch + 1), raw);
+      else if (half) fetch_half(16 * nfull, raw);
+    };
+    if (16 * ch + 16 <= npos) {   // uniform: only entering vectors
+      accumulate(VecsPerLane<4>(), raw, none, next);
+    } else {
+      uint32_t sign[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int m = 16 * ch + 4 * g + 2 * k;
+        sign[k] = (m >= npos ? 0x00008000u : 0u) | (m + 1 >= npos ? 0x80000000u : 0u);
+      }
+      accumulate(VecsPerLane<4>(), raw, sign, next);
+    }
+  }
+  if (half) {
+    const int m = 16 * nfull + 2 * g;
+    const uint32_t sign[2] = {(m >= npos ? 0x00008000u : 0u) | (m + 1 >= npos ? 0x80000000u : 0u), 0u};
+    accumulate(VecsPerLane<2>(), raw, sign, [] {});
+  }
+}
+
+// n S from LDS (the previous pixel's S), for classes that do not keep it.
+template <int P, int Q>
+__device__ __forceinline__ void split_reload(const float2* sS, int n, SplitAcc<P, Q>& acc) {
+  constexpr int NB = SplitAcc<P, Q>::NB;
+  int trow = 4 * (threadIdx.x >> 4), tcol = threadIdx.x & 15;
+  if constexpr (kOpaqueStore<P, Q>) asm volatile("" : "+v"(trow), "+v"(tcol));
+  const float fn = float(n);
+#pragma unroll
+  for (int I = 0; I < NB; ++I)
+#pragma unroll
+    for (int J = I; J < NB; ++J)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int t = I * NB - I * (I - 1) / 2 + J - I;
+        float2 v = make_float2(0.f, 0.f);
+        if (tile_in<P, Q>(I, J, trow + q4, tcol)) v = tile_get<P, Q>(sS, I, J, trow + q4, tcol);
+        acc.r[t][q4] = v.x * fn;
+        acc.i[t][q4] = v.y * fn;
+      }
+  wave_sync();   // every lane has reloaded its part
+}
+
+// S = acc / n to LDS.
+template <int P, int Q>
+__device__ __forceinline__ void split_store(const SplitAcc<P, Q>& acc, int n, float2* sS) {
+  constexpr int NB = SplitAcc<P, Q>::NB;
+  int trow = 4 * (threadIdx.x >> 4), tcol = threadIdx.x & 15;
+  if constexpr (kOpaqueStore<P, Q>) asm volatile("" : "+v"(trow), "+v"(tcol));
+  const float inv_n = 1.f / float(n);
+#pragma unroll
+  for (int I = 0; I < NB; ++I)
+#pragma unroll
+    for (int J = I; J < NB; ++J)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int t = I * NB - I * (I - 1) / 2 + J - I;
+        const float2 v = make_float2(acc.r[t][q4] * inv_n, acc.i[t][q4] * inv_n);
+        if constexpr (Q == 16) {   // a tile is a block, stored whole (one writer per element)
+          sS[sblk<P, Q>(I, J) + (trow + q4) * (Q + 1) + tcol] = v;
+        } else {
+          if (tile_keep<P, Q>(I, J, trow + q4, tcol)) tile_put<P, Q>(sS, I, J, trow + q4, tcol, v);
+        }
+      }
   wave_sync();
 }
 
@@ -986,9 +1263,6 @@ __device__ __forceinline__ void scm_fp32_delta(const float2* xwin, int64_t plane
 //   Im S tiles: v_mfma_f32_16x16x16_bf16 on single components,
 //     im_I re_J^T + (-re_I) im_J^T; the operands are half-word gathers (and
 //     one sign flip) of the loaded pairs.
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-
 __device__ __forceinline__ void split_bf16(const float2 (&v)[4], bf8& hi, bf8& lo) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -1006,11 +1280,6 @@ __device__ __forceinline__ bf8 swap_neg(bf8 y) {
   for (int e = 0; e < 4; ++e) w[e] = ((w[e] >> 16) | (w[e] << 16)) ^ 0x80000000u;
   return __builtin_bit_cast(bf8, w);
 }
-
-typedef short s4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u2 __attribute__((ext_vector_type(2)));
-
-
 
 // re (low halves) and im (high halves) of two packed pairs, as one dword
 __device__ __forceinline__ uint32_t lo_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
@@ -1422,7 +1691,7 @@ struct Lds {
   // batched tail's basis exchange, and the FP32 path's diagonal-tile transpose
   static constexpr size_t kB = sizeof(float2) * Q * (Q + 2);
   static constexpr size_t kT = sizeof(EC) * RBM * Q * G;
-  static constexpr size_t kP = PREC == 1 ? 0 : sizeof(float) * NB * 256;
+  static constexpr size_t kP = (PREC == 1 || kSplitCov<P, Q>) ? 0 : sizeof(float) * NB * 256;
   static constexpr size_t kBT = kB > kT ? (kB > kP ? kB : kP) : (kT > kP ? kT : kP);
   static constexpr size_t oUA = 0;                                        // EC[P*RAM]
   static constexpr size_t oAh = oUA + sizeof(EC) * P * RAM;               // EC[P*P]
@@ -1431,9 +1700,10 @@ struct Lds {
   static constexpr size_t oS = (oBT + kBT + 15) / 16 * 16;                // float2[P(P+1)/2][Q][Q+1]
   static constexpr size_t oA = oS + sizeof(float2) * (P * (P + 1) / 2) * Q * (Q + 1);   // float2[P*P]
   static constexpr size_t oQidx = oA + sizeof(float2) * P * P;            // int64[G]
-  static constexpr size_t oOff = oQidx + sizeof(int64_t) * G;             // uint32[kMaxN + kOffPad]
-  static constexpr size_t oDelta = oOff + sizeof(uint32_t) * (kMaxN + kOffPad);   // uint32[3][2][kMaxDelta + 8] (FP32)
-  static constexpr size_t oQflag = oDelta + (PREC ? 0 : sizeof(uint32_t) * 6 * (kMaxDelta + 8));   // int[G]
+  static constexpr size_t oOff = (oQidx + sizeof(int64_t) * G + 15) / 16 * 16;   // uint32[kMaxN + kOffPad]
+  static constexpr size_t oDelta = oOff + sizeof(uint32_t) * (kMaxN + kOffPad);   // uint32[nDelta] (FP32)
+  static constexpr int nDelta = PREC ? 0 : kSplitCov<P, Q> ? 3 * kDeltaList : 6 * (kMaxDelta + 8);
+  static constexpr size_t oQflag = oDelta + sizeof(uint32_t) * nDelta;   // int[G]
   static constexpr size_t oQit = oQflag + sizeof(int) * G;                // int[G]
   static constexpr size_t oQeta = oQit + sizeof(int) * G;                 // float[G]
   static constexpr size_t bytes = ((oQeta + sizeof(float) * G) + 15) / 16 * 16;
@@ -1460,7 +1730,6 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
   uint32_t* const sOffB = reinterpret_cast<uint32_t*>(lds + L::oOff);
   // sliding window: per move, the entering then the leaving vectors
   uint32_t* const sDelta = reinterpret_cast<uint32_t*>(lds + L::oDelta);
-  constexpr int KD = kMaxDelta + 8;
   float2* const sA = reinterpret_cast<float2*>(lds + L::oA);
   EC* const sUA = reinterpret_cast<EC*>(lds + L::oUA);
   EC* const sAh = reinterpret_cast<EC*>(lds + L::oAh);
@@ -1483,13 +1752,20 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
   for (int m = lane; m < kMaxN + kOffPad; m += 64)
     sOffB[m] = (m < n) ? uint32_t(((int(prm.st[2 * m]) * W + int(prm.st[2 * m + 1])) * Q - prm.st_min) * kSample)
                        : kOut;
-  for (int m = lane; m < (PREC ? 0 : 6 * KD); m += 64) {
-    const int t = m / KD, e = m - t * KD, mv = t >> 1;
-    const int cnt = (t & 1) ? prm.nrem[mv] : prm.nadd[mv];
+  // per move: one list, entering then leaving vectors (scm_split), or two
+  // lists of KD (scm_fp32_delta)
+  constexpr int KD = kMaxDelta + 8;
+  for (int m = lane; m < L::nDelta; m += 64) {
+    constexpr int per = kSplitCov<P, Q> ? kDeltaList : 2 * KD;
+    const int mv = m / per;
+    int e = m - mv * per;
+    const int na = prm.nadd[mv], nr = prm.nrem[mv];   // each <= kMaxDelta (negative: never slides)
+    const bool rem = kSplitCov<P, Q> ? e >= na : e >= KD;
+    e -= rem ? (kSplitCov<P, Q> ? na : KD) : 0;
     uint32_t off = kOut;
-    if (e < cnt) {   // cnt <= kMaxDelta
-      const int dr = (t & 1) ? prm.drem[mv][2 * e] : prm.dadd[mv][2 * e];
-      const int dc = (t & 1) ? prm.drem[mv][2 * e + 1] : prm.dadd[mv][2 * e + 1];
+    if (na >= 0 && e < (rem ? nr : na)) {
+      const int dr = rem ? prm.drem[mv][2 * e] : prm.dadd[mv][2 * e];
+      const int dc = rem ? prm.drem[mv][2 * e + 1] : prm.dadd[mv][2 * e + 1];
       off = uint32_t(((dr * W + dc) * Q - prm.st_min) * kSample);
     }
     sDelta[m] = off;
@@ -1573,6 +1849,7 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
   // and runs start on a chain, so the choice is the same for every
   // decomposition.
   bool chain = false;
+  SplitAcc<P, Q> acc;   // n S of the pixel processed last (kKeepAcc)
   bool ua_ok = false;   // ua (r_a = 1) or sUA holds the U_A of the pixel processed last
   EC ua[P];
 #pragma unroll
@@ -1616,12 +1893,24 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
     // MFMAs, so they always take the full sum: no sliding-window residue)
     const int mv = tiled_move(first + it, H, W, kChainNarrow);
     const bool slide = PREC == 0 && MODE == kModeRun && left_ok && mv >= 0 && prm.nadd[0] >= 0;
-    if constexpr (PREC != 1) {
+    if constexpr (PREC != 1 && kSplitCov<P, Q>) {
+      if (slide) {
+        if constexpr (!kKeepAcc<P, Q>) split_reload<P, Q>(sS, n, acc);
+      } else {
+#pragma unroll
+        for (int t = 0; t < SplitAcc<P, Q>::NT; ++t) acc.r[t] = acc.i[t] = f4{0.f, 0.f, 0.f, 0.f};
+      }
+      scm_split<P, Q, MODE == kModeProbe ? 3 : 1>(prm.x + win, plane, prm.rec_bytes,
+                                                  slide ? sDelta + mv * kDeltaList : sOffB, slide ? prm.nadd[mv] : n,
+                                                  slide ? prm.nadd[mv] + prm.nrem[mv] : n, loff, acc);
+      split_store<P, Q>(acc, n, sS);
+    } else if constexpr (PREC != 1) {
+      SSums<P> ss{};   // gathered for the Doppler bank kernels only
       if (slide)
         scm_fp32_delta<P, Q>(prm.x + win, plane, prm.rec_bytes, sDelta + 2 * mv * KD, prm.nadd[mv],
-                             sDelta + (2 * mv + 1) * KD, prm.nrem[mv], loff, n, sS);
+                             sDelta + (2 * mv + 1) * KD, prm.nrem[mv], loff, n, sS, ss);
       else
-        scm_fp32<P, Q>(prm.x + win, plane, prm.rec_bytes, sOffB, loff, n, sS, reinterpret_cast<float*>(sBT));
+        scm_fp32<P, Q>(prm.x + win, plane, prm.rec_bytes, sOffB, loff, n, sS, reinterpret_cast<float*>(sBT), ss);
     } else {
       scm_bf16x3<P, Q>(prm.xs + win, prm.xs + P * plane + win, plane, prm.rec_bytes / 2, sOffB, loff, n, sS);
     }
@@ -2027,14 +2316,27 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
   if (nq > 0) tail(nq);
 }
 
+}  // namespace
+}  // namespace kstap
+
+#include "kstap_bank.h"
+
+namespace kstap {
+namespace {
+
+// Which statistic a kernel is compiled for: the plain one, its variants
+// (filter, enhancement, passes), or the FP32 Doppler bank (kstap_bank.h).
+enum Variant { kPlain = 0, kVariant = 1, kBank = 2 };
+
 // Whole frame (run mode) or pixel list (probe mode).  Run mode: workgroup ids
 // are remapped so each of the 8 XCDs takes a contiguous share of the frame.
 // VAR: the statistic variants (filter, Doppler bank, enhancement, passes) are
 // compiled into a kernel of their own, so that the plain statistic keeps its
 // register budget.
-template <int P, int Q, int RBM, int MODE, int PREC, bool VAR = false>
+template <int P, int Q, int RBM, int MODE, int PREC, int VAR = kPlain>
 __global__ __launch_bounds__(64, 2) void kstap_kernel(const KParams prm) {
-  __shared__ __attribute__((aligned(16))) char lds[Lds<P, Q, RBM, PREC>::bytes];
+  constexpr bool kBankKernel = VAR == kBank && PREC == 0;
+  __shared__ __attribute__((aligned(16))) char lds[kBankKernel ? BankLds<P, Q, RBM>::bytes : Lds<P, Q, RBM, PREC>::bytes];
   int64_t first, count;
   if (MODE == kModeRun) {
     const int per = gridDim.x >> 3;   // grid is a multiple of 8 (one share per XCD)
@@ -2049,7 +2351,8 @@ __global__ __launch_bounds__(64, 2) void kstap_kernel(const KParams prm) {
     count = prm.npix - first;
     if (count > prm.pix_per_block) count = prm.pix_per_block;
   }
-  run_pixels<P, Q, RBM, MODE, PREC, VAR>(prm, first, count, lds);
+  if constexpr (kBankKernel) run_pixels_bank<P, Q, RBM>(prm, first, count, lds);
+  else run_pixels<P, Q, RBM, MODE, PREC, VAR != kPlain>(prm, first, count, lds);
 }
 
 // Persistent batched kernel: every workgroup pops work items (runs of `ppb`
@@ -2851,8 +3154,11 @@ int launch_one(int mode, const KParams& prm, hipStream_t stream) {
   if (units <= 0) return hipSuccess;
   int64_t grid = (mode == kModeRun) ? ((units + 7) / 8) * 8 : units;
   if (grid > 0x7fffffff) return hipErrorInvalidValue;
-  if (mode == kModeRun && has_variants(prm))
-    hipLaunchKernelGGL((kstap_kernel<P, Q, RBM, kModeRun, PREC, true>), dim3(unsigned(grid)), dim3(64), 0, stream,
+  if (mode == kModeRun && has_variants(prm) && prm.nbank > 0)
+    hipLaunchKernelGGL((kstap_kernel<P, Q, RBM, kModeRun, PREC, PREC == 0 ? kBank : kVariant>), dim3(unsigned(grid)),
+                       dim3(64), 0, stream, prm);
+  else if (mode == kModeRun && has_variants(prm))
+    hipLaunchKernelGGL((kstap_kernel<P, Q, RBM, kModeRun, PREC, kVariant>), dim3(unsigned(grid)), dim3(64), 0, stream,
                        prm);
   else if (mode == kModeRun)
     hipLaunchKernelGGL((kstap_kernel<P, Q, RBM, kModeRun, PREC>), dim3(unsigned(grid)), dim3(64), 0, stream, prm);
