@@ -1051,7 +1051,7 @@ typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 
 template <int V>
-struct VecsPerLane {
+struct Int {   // a constant as a lambda's argument
   static constexpr int value = V;
 };
 
@@ -1068,8 +1068,27 @@ __device__ __forceinline__ void split3(float a, float b, uint32_t (&part)[3]) {
   }
 }
 
-// n S += sum over the vectors list[0 .. npos) - sum over list[npos .. cnt):
-// byte offsets in LDS, kOut past cnt for 32 entries.  PF chunks are in flight:
+// Raw samples of a chunk: rows of block I, vectors e of this lane.
+template <int P, int Q>
+struct SplitRaw {
+  float2 v[(P * Q + 15) / 16][4];
+};
+// A list of cnt vectors takes split_full(cnt) whole chunks (a remainder of 9
+// to 15 vectors fills one, zeros past cnt) and, for a remainder of 1 to 8, a
+// half chunk, whose vectors lie in the list two to a group of four entries
+// (4g, 4g + 1: vectors 2g, 2g + 1 of the half chunk), so that every chunk is
+// fetched the same way.
+__device__ __forceinline__ int split_full(int cnt) { return (cnt + 7) >> 4; }
+// The vector at list entry m, or -1.
+__device__ __forceinline__ int split_entry(int m, int cnt) {
+  const int whole = 16 * split_full(cnt);
+  if (m >= whole) m = (m & 3) < 2 ? whole + 2 * ((m - whole) >> 2) + (m & 3) : cnt;
+  return m < cnt ? m : -1;
+}
+
+// n S += sum over the vectors [0, npos) - sum over [npos, cnt) of a list of
+// byte offsets in LDS (entries as split_entry, kOut where there is no vector;
+// the chunk past the last is fetched and unused).  PF chunks are in flight:
 // one where another wavefront fills the wait and the windows are in L2 (run
 // mode); three for the pixel lists of the probe, whose windows come from HBM
 // (no leaving vectors there).
@@ -1082,26 +1101,17 @@ __device__ __forceinline__ void scm_split(const float2* xwin, int64_t plane, uin
   __amdgpu_buffer_rsrc_t rs[NB];
 #pragma unroll
   for (int I = 0; I < NB; ++I) rs[I] = block_rsrc<Q>(xwin, plane, rec, I);
-  float2 ring[PF][NB][4];   // chunk ch in ring[ch % PF], refetched as soon as its vectors are split
-  auto fetch = [&](int m, float2 (&v)[NB][4]) __attribute__((always_inline)) {
-    const uint4 o = *reinterpret_cast<const uint4*>(list + m + 4 * g);
+  auto fetch = [&](int ch, SplitRaw<P, Q>& v) __attribute__((always_inline)) {
+    const uint4 o = *reinterpret_cast<const uint4*>(list + 16 * ch + 4 * g);
     const uint32_t off[4] = {o.x, o.y, o.z, o.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int I = 0; I < NB; ++I) v[I][e] = bload(rs[I], loff[I] + off[e]);
-  };
-  auto fetch_half = [&](int m, float2 (&v)[NB][4]) __attribute__((always_inline)) {
-    const uint2 o = *reinterpret_cast<const uint2*>(list + m + 2 * g);
-    const uint32_t off[2] = {o.x, o.y};
-#pragma unroll
-    for (int e = 0; e < 2; ++e)
-#pragma unroll
-      for (int I = 0; I < NB; ++I) v[I][e] = bload(rs[I], loff[I] + off[e]);
+      for (int I = 0; I < NB; ++I) v.v[I][e] = bload(rs[I], loff[I] + off[e]);
   };
   // MFMAs of one chunk of V vectors per lane; sign[k]: sign bits of the pair k;
   // `then` runs once the raw samples are consumed
-  auto accumulate = [&](auto vc, const float2 (&raw)[NB][4], const uint32_t (&sign)[2], auto then)
+  auto accumulate = [&](auto vc, const SplitRaw<P, Q>& raw, const uint32_t (&sign)[2], auto then)
                         __attribute__((always_inline)) {
     constexpr int V = decltype(vc)::value;
     uint32_t y[NB][3][V];
@@ -1110,8 +1120,8 @@ __device__ __forceinline__ void scm_split(const float2* xwin, int64_t plane, uin
 #pragma unroll
       for (int k = 0; k < V / 2; ++k) {
         uint32_t re[3], im[3];
-        split3(raw[I][2 * k].x, raw[I][2 * k + 1].x, re);
-        split3(raw[I][2 * k].y, raw[I][2 * k + 1].y, im);
+        split3(raw.v[I][2 * k].x, raw.v[I][2 * k + 1].x, re);
+        split3(raw.v[I][2 * k].y, raw.v[I][2 * k + 1].y, im);
 #pragma unroll
         for (int e = 0; e < 3; ++e) {
           y[I][e][2 * k] = re[e];
@@ -1124,6 +1134,7 @@ __device__ __forceinline__ void scm_split(const float2* xwin, int64_t plane, uin
     constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};   // small products first
 #pragma unroll
     for (int J = NB - 1; J >= 0; --J) {
+      __builtin_amdgcn_sched_barrier(0);   // one block's column operands at a time
       uint32_t cr[3][V], ci[3][V];
 #pragma unroll
       for (int e = 0; e < 3; ++e)
@@ -1155,38 +1166,33 @@ __device__ __forceinline__ void scm_split(const float2* xwin, int64_t plane, uin
         }
     }
   };
-  const int nfull = (cnt + 7) >> 4;          // a remainder of 9 to 15 fills a chunk (zeros past cnt)
-  const bool half = cnt > 16 * nfull;        // 1 to 8 vectors left
+  const int nfull = split_full(cnt);
+  const bool half = cnt > 16 * nfull;
   const uint32_t none[2] = {0u, 0u};
   if constexpr (PF > 1) {
-    float2 rest[NB][4];
-    if (half) fetch_half(16 * nfull, rest);
+    SplitRaw<P, Q> ring[PF], rest;   // chunk ch in ring[ch % PF], refetched as soon as its vectors are split
+    fetch(nfull, rest);
 #pragma unroll
-    for (int sl = 0; sl < PF; ++sl)
-      if (sl < nfull) fetch(16 * sl, ring[sl]);
+    for (int sl = 0; sl < PF; ++sl) fetch(sl < nfull ? sl : nfull, ring[sl]);
 #pragma unroll 1
     for (int ch0 = 0; ch0 < nfull; ch0 += PF) {
 #pragma unroll
       for (int sl = 0; sl < PF; ++sl)
         if (ch0 + sl < nfull)
-          accumulate(VecsPerLane<4>(), ring[sl], none, [&]() __attribute__((always_inline)) {
-            if (ch0 + sl + PF < nfull) fetch(16 * (ch0 + sl + PF), ring[sl]);
+          accumulate(Int<4>(), ring[sl], none, [&]() __attribute__((always_inline)) {
+            fetch(ch0 + sl + PF < nfull ? ch0 + sl + PF : nfull, ring[sl]);
           });
     }
-    if (half) accumulate(VecsPerLane<2>(), rest, none, [] {});
+    if (half) accumulate(Int<2>(), rest, none, [] {});
     return;
   }
-  float2(&raw)[NB][4] = ring[0];
-  if (nfull > 0) fetch(0, raw);
-  else fetch_half(0, raw);
+  SplitRaw<P, Q> raw;   // the chunk in flight: refetched as soon as its vectors are split
+  fetch(0, raw);
 #pragma unroll 1
   for (int ch = 0; ch < nfull; ++ch) {
-    auto next = [&]() __attribute__((always_inline)) {
-      if (ch + 1 < nfull) fetch(16 * (ch + 1), raw);
-      else if (half) fetch_half(16 * nfull, raw);
-    };
+    auto next = [&]() __attribute__((always_inline)) { fetch(ch + 1, raw); };
     if (16 * ch + 16 <= npos) {   // uniform: only entering vectors
-      accumulate(VecsPerLane<4>(), raw, none, next);
+      accumulate(Int<4>(), raw, none, next);
     } else {
       uint32_t sign[2];
 #pragma unroll
@@ -1194,13 +1200,13 @@ __device__ __forceinline__ void scm_split(const float2* xwin, int64_t plane, uin
         const int m = 16 * ch + 4 * g + 2 * k;
         sign[k] = (m >= npos ? 0x00008000u : 0u) | (m + 1 >= npos ? 0x80000000u : 0u);
       }
-      accumulate(VecsPerLane<4>(), raw, sign, next);
+      accumulate(Int<4>(), raw, sign, next);
     }
   }
   if (half) {
     const int m = 16 * nfull + 2 * g;
     const uint32_t sign[2] = {(m >= npos ? 0x00008000u : 0u) | (m + 1 >= npos ? 0x80000000u : 0u), 0u};
-    accumulate(VecsPerLane<2>(), raw, sign, [] {});
+    accumulate(Int<2>(), raw, sign, [] {});
   }
 }
 
@@ -1226,10 +1232,26 @@ __device__ __forceinline__ void split_reload(const float2* sS, int n, SplitAcc<P
   wave_sync();   // every lane has reloaded its part
 }
 
-// S = acc / n to LDS.
+// Where a pixel's S is only handed from the accumulators to its slots (the
+// accumulators keep it, or the next pixel starts anew), q = 16 passes it
+// through LDS in two phases, block row 0 and then the others, in half the
+// space (P = 3: three of the six blocks at a time).
 template <int P, int Q>
-__device__ __forceinline__ void split_store(const SplitAcc<P, Q>& acc, int n, float2* sS) {
+constexpr bool kPhased = kKeepAcc<P, Q> && Q == 16 && P == 3;
+template <int P, int Q>
+constexpr int kBlocksLds = kPhased<P, Q> ? P : P * (P + 1) / 2;
+// LDS offset of block (i, j), i <= j
+template <int P, int Q>
+__device__ __forceinline__ int lblk(int i, int j) {
+  return sblk<P, Q>(i, j) - (kPhased<P, Q> && i > 0 ? P * Q * (Q + 1) : 0);
+}
+
+// S = acc / n to LDS: the 16-row blocks [lo, hi) of its rows.
+template <int P, int Q>
+__device__ __forceinline__ void split_store(const SplitAcc<P, Q>& acc, int n, float2* sS, int lo, int hi) {
   constexpr int NB = SplitAcc<P, Q>::NB;
+  // opaque, so that the element addresses are computed here for every pixel
+  // rather than hoisted out of the caller's pixel loop and spilled
   int trow = 4 * (threadIdx.x >> 4), tcol = threadIdx.x & 15;
   if constexpr (kOpaqueStore<P, Q>) asm volatile("" : "+v"(trow), "+v"(tcol));
   const float inv_n = 1.f / float(n);
@@ -1239,10 +1261,11 @@ __device__ __forceinline__ void split_store(const SplitAcc<P, Q>& acc, int n, fl
     for (int J = I; J < NB; ++J)
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
+        if (I < lo || I >= hi) continue;
         const int t = I * NB - I * (I - 1) / 2 + J - I;
         const float2 v = make_float2(acc.r[t][q4] * inv_n, acc.i[t][q4] * inv_n);
         if constexpr (Q == 16) {   // a tile is a block, stored whole (one writer per element)
-          sS[sblk<P, Q>(I, J) + (trow + q4) * (Q + 1) + tcol] = v;
+          sS[lblk<P, Q>(I, J) + (trow + q4) * (Q + 1) + tcol] = v;
         } else {
           if (tile_keep<P, Q>(I, J, trow + q4, tcol)) tile_put<P, Q>(sS, I, J, trow + q4, tcol, v);
         }
@@ -1288,12 +1311,12 @@ __device__ __forceinline__ uint32_t hi_halves(uint32_t a, uint32_t b) { return _
 template <int P, int Q>
 __device__ __forceinline__ void scm_bf16x3(const uint32_t* hwin, const uint32_t* lwin, int64_t plane, uint32_t rec,
                                            const uint32_t* sOffB, const uint32_t (&loff)[(P * Q + 15) / 16], int n,
-                                           float2* sS) {
-  constexpr int PQ = P * Q;
-  constexpr int NB = (PQ + 15) / 16;
+                                           SplitAcc<P, Q>& acc) {
+  constexpr int NB = (P * Q + 15) / 16;
   constexpr int NT = NB * (NB + 1) / 2;
   const int lane = threadIdx.x;
-  f4 accR[NT], accI[NT];
+  f4(&accR)[NT] = acc.r;
+  f4(&accI)[NT] = acc.i;
 #pragma unroll
   for (int t = 0; t < NT; ++t) accR[t] = accI[t] = f4{0.f, 0.f, 0.f, 0.f};
   const int nch = (n + 15) >> 4;
@@ -1369,25 +1392,6 @@ __device__ __forceinline__ void scm_bf16x3(const uint32_t* hwin, const uint32_t*
 #pragma unroll
   for (int sl = 0; sl < PF - 1; ++sl)
     if (ch0 + sl < nch) accumulate(ring[sl]);
-  const float inv_n = 1.f / float(n);
-  // opaque, so that the element addresses are computed here for every pixel
-  // rather than hoisted out of the caller's pixel loop and spilled
-  int trow = 4 * (lane >> 4), tcol = lane & 15;
-  asm volatile("" : "+v"(trow), "+v"(tcol));
-  int t = 0;
-#pragma unroll
-  for (int I = 0; I < NB; ++I)
-#pragma unroll
-    for (int J = I; J < NB; ++J, ++t)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int tr = trow + q4;
-        if (tile_keep<P, Q>(I, J, tr, tcol)) {
-          const float2 v = make_float2(accR[t][q4] * inv_n, accI[t][q4] * inv_n);
-          tile_put<P, Q>(sS, I, J, tr, tcol, v);
-        }
-      }
-  wave_sync();
 }
 
 // ------------------------------------------------------------ kernel body
@@ -1646,6 +1650,14 @@ __device__ __forceinline__ void tail_batch(const KParams& prm, const float2 (&Bq
   lds_sync<WAVE_LOCAL>();
 }
 
+}  // namespace
+}  // namespace kstap
+
+#include "kstap_tail.h"
+
+namespace kstap {
+namespace {
+
 // PREC 0: FP32 covariance, FP32 eigensolves and statistic.
 // PREC 1: split-BF16 covariance, FP64 eigensolves and statistic.
 // PREC 2: FP32 covariance (full sums, no sliding window), FP64 eigensolves
@@ -1679,6 +1691,28 @@ struct Slots {
   static constexpr int N = (NS * (2 / C) + 63) / 64;   // slots per lane
 };
 
+// Queued time factors wait for the batched tail in LDS, as slots, where S
+// leaves room for them (kKeepAcc: it is in LDS only in passing); else as one
+// row per lane in registers.  In registers (32 for q = 16) they raised the
+// covariance phase over the register file: it spilled, and waited for each
+// chunk's loads as soon as they were issued.
+template <int P, int Q>
+constexpr bool kQueueLds = kKeepAcc<P, Q>;
+
+// Row k of the Hermitian q x q matrix whose slots are qb.
+template <int P, int Q>
+__device__ __forceinline__ void queue_row(const float2* qb, int k, float2 (&row)[Q]) {
+#pragma unroll
+  for (int l = 0; l < Q; ++l) {
+    int d = l - k;
+    d += d < 0 ? Q : 0;
+    const bool up = d < Q / 2 || (d == Q / 2 && k < Q / 2), hi = k >= Q / 2;
+    const int e = d == 0 ? (Q / 2 - 1) * Q + (hi ? k : k + Q / 2) : up ? (d - 1) * Q + k : (Q - d - 1) * Q + l;
+    const float2 b = qb[e];
+    row[l] = make_float2(d == 0 && hi ? b.y : b.x, d == 0 ? 0.f : up ? b.y : -b.y);
+  }
+}
+
 // LDS carve-out of one pixel pipeline (one workgroup), largest alignment first.
 template <int P, int Q, int RBM, int PREC>
 struct Lds {
@@ -1687,19 +1721,21 @@ struct Lds {
   static constexpr int RAM = (P < kMaxRA) ? P : kMaxRA;
   static constexpr int G = Groups<Q>::G;
   static constexpr int NB = (PQ + 15) / 16;
-  // B / tail / transpose scratch: the time factor B (q rows of q + 2), the
-  // batched tail's basis exchange, and the FP32 path's diagonal-tile transpose
-  static constexpr size_t kB = sizeof(float2) * Q * (Q + 2);
-  static constexpr size_t kT = sizeof(EC) * RBM * Q * G;
+  // B / tail / transpose scratch: the time factor B (q rows of q + 2; classes
+  // that queue rows), the batched tail's basis exchange, and the FP32 path's
+  // diagonal-tile transpose
+  static constexpr size_t kB = kQueueLds<P, Q> ? 0 : sizeof(float2) * Q * (Q + 2);
+  static constexpr size_t kT = tail_scratch_bytes<RBM, Q, G, EC>;
   static constexpr size_t kP = (PREC == 1 || kSplitCov<P, Q>) ? 0 : sizeof(float) * NB * 256;
   static constexpr size_t kBT = kB > kT ? (kB > kP ? kB : kP) : (kT > kP ? kT : kP);
   static constexpr size_t oUA = 0;                                        // EC[P*RAM]
   static constexpr size_t oAh = oUA + sizeof(EC) * P * RAM;               // EC[P*P]
   static constexpr size_t oQUA = oAh + sizeof(EC) * P * P;                // EC[G][P*RAM]
-  static constexpr size_t oBT = oQUA + sizeof(EC) * G * P * RAM;          // kBT bytes
+  static constexpr size_t oBT = (oQUA + sizeof(EC) * G * P * RAM + 15) / 16 * 16;   // kBT bytes
   static constexpr size_t oS = (oBT + kBT + 15) / 16 * 16;                // float2[P(P+1)/2][Q][Q+1]
-  static constexpr size_t oA = oS + sizeof(float2) * (P * (P + 1) / 2) * Q * (Q + 1);   // float2[P*P]
-  static constexpr size_t oQidx = oA + sizeof(float2) * P * P;            // int64[G]
+  static constexpr size_t oA = oS + sizeof(float2) * kBlocksLds<P, Q> * Q * (Q + 1);   // float2[P*P]
+  static constexpr size_t oQB = oA + sizeof(float2) * P * P;              // float2[G][NS] (kQueueLds)
+  static constexpr size_t oQidx = oQB + (kQueueLds<P, Q> ? sizeof(float2) * G * Slots<P, Q>::NS : 0);   // int64[G]
   static constexpr size_t oOff = (oQidx + sizeof(int64_t) * G + 15) / 16 * 16;   // uint32[kMaxN + kOffPad]
   static constexpr size_t oDelta = oOff + sizeof(uint32_t) * (kMaxN + kOffPad);   // uint32[nDelta] (FP32)
   static constexpr int nDelta = PREC ? 0 : kSplitCov<P, Q> ? 3 * kDeltaList : 6 * (kMaxDelta + 8);
@@ -1749,9 +1785,11 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
   // samples are complex64 (8 bytes) or, on the mixed path, BF16 pairs (4)
   constexpr int kSample = PREC == 1 ? 4 : 8;
   wave_sync();
-  for (int m = lane; m < kMaxN + kOffPad; m += 64)
-    sOffB[m] = (m < n) ? uint32_t(((int(prm.st[2 * m]) * W + int(prm.st[2 * m + 1])) * Q - prm.st_min) * kSample)
-                       : kOut;
+  for (int e = lane; e < kMaxN + kOffPad; e += 64) {
+    const int m = (PREC != 1 && kSplitCov<P, Q>) ? split_entry(e, n) : (e < n ? e : -1);
+    sOffB[e] = (m >= 0) ? uint32_t(((int(prm.st[2 * m]) * W + int(prm.st[2 * m + 1])) * Q - prm.st_min) * kSample)
+                        : kOut;
+  }
   // per move: one list, entering then leaving vectors (scm_split), or two
   // lists of KD (scm_fp32_delta)
   constexpr int KD = kMaxDelta + 8;
@@ -1760,6 +1798,10 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
     const int mv = m / per;
     int e = m - mv * per;
     const int na = prm.nadd[mv], nr = prm.nrem[mv];   // each <= kMaxDelta (negative: never slides)
+    if constexpr (kSplitCov<P, Q>) {
+      e = na >= 0 ? split_entry(e, na + nr) : -1;
+      if (e < 0) e = na + nr;   // no vector
+    }
     const bool rem = kSplitCov<P, Q> ? e >= na : e >= KD;
     e -= rem ? (kSplitCov<P, Q> ? na : KD) : 0;
     uint32_t off = kOut;
@@ -1784,9 +1826,10 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
     loff[I] = (rho < PQ) ? uint32_t(((ch - (16 * I) / Q) * plane + j) * kSample) : kOut;
   }
 
-  // queue of pixels waiting for the batched tail: lane (g, k) holds row k of
-  // the Hermitian time factor of queued pixel g
+  // queue of pixels waiting for the batched tail: their slots in LDS, or lane
+  // (g, k) holds row k of the Hermitian time factor of queued pixel g
   const int tg = lane / QP, tk = lane % QP;
+  float2* const sQB = reinterpret_cast<float2*>(lds + L::oQB);
   float2 Bq[Q];
 #pragma unroll
   for (int l = 0; l < Q; ++l) Bq[l] = cz();
@@ -1807,9 +1850,36 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
   int64_t qchain = -1, bchain = -2;   // chain of the queued pixels, of the last batch
   auto tail = [&](int nfill) __attribute__((always_inline)) {
     const bool keep = kWarmTail && bchain == qchain && vbw_ok;
-    bool ok;
-    tail_batch<P, Q, RBM, MODE, EC, false, VAR>(prm, Bq, tg, nfill, sQflag, sQidx, sQeta, sQit, sQUA, tail_scratch,
-                                                PREC ? 1e-10 : 2e-6, vbw, keep, ok);
+    bool ok = false;
+    if constexpr (kQueueLds<P, Q>) {
+      int lanev = lane;   // per batch: no address hoisted out of the pixel loop
+      asm volatile("" : "+v"(lanev));
+      const int k = lanev % QP;
+      queue_row<P, Q>(sQB + (lanev / QP) * NS, k < Q ? k : 0, Bq);   // empty slots: whatever is there, unused
+    }
+    if constexpr (VAR) {
+      tail_batch<P, Q, RBM, MODE, EC, false, true>(prm, Bq, tg, nfill, sQflag, sQidx, sQeta, sQit, sQUA, tail_scratch,
+                                                   PREC ? 1e-10 : 2e-6, vbw, keep, ok);
+    } else {
+      auto rows = [&](auto rank) __attribute__((always_inline)) {
+        tail_rows<P, Q, RBM, decltype(rank)::value, MODE, EC>(prm, Bq, nfill, sQflag, sQidx, sQeta, sQit, sQUA,
+                                                              reinterpret_cast<char*>(sBT), PREC ? 1e-10 : 2e-6, vbw,
+                                                              keep, ok);
+      };
+      // r_b as a constant (r_b > 4 takes the RBM = 8 classes)
+      if constexpr (RBM == 4) {
+        if (r_b == 4) rows(Int<4>());
+        else if (r_b == 3) rows(Int<3>());
+        else if (r_b == 2) rows(Int<2>());
+        else if (r_b == 1) rows(Int<1>());
+        else rows(Int<0>());
+      } else {
+        if (r_b == 8) rows(Int<8>());
+        else if (r_b == 7) rows(Int<7>());
+        else if (r_b == 6) rows(Int<6>());
+        else rows(Int<5>());
+      }
+    }
     if constexpr (kWarmTail) {
       bchain = qchain;
       const int src = (G - 1 - tg) * QP + tk;
@@ -1854,13 +1924,19 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
   EC ua[P];
 #pragma unroll
   for (int i = 0; i < P; ++i) ua[i] = czero<EC>();
-  for (int64_t it = 0; it < count; ++it) {
+  int ur = 0, uc = 0;   // first pixel of the current unit: found once per unit, not by division per pixel
+  auto pixel = [&](int64_t it) __attribute__((always_inline)) {
     int64_t idx;
     int r, c;
     const bool left_ok = chain;
     chain = false;
+    // position k of the unit's snake: row k / 4, alternately left to right and back
+    const int k = int(first + it) & (kUnit * kUnit - 1);
     if (MODE == kModeRun) {
-      if (!tiled_pixel(first + it, H, W, &r, &c)) continue;
+      if (it == 0 || k == 0) tiled_pixel(first + it - k, H, W, &ur, &uc);
+      r = ur + k / kUnit;
+      c = uc + ((k / kUnit & 1) ? kUnit - 1 - k % kUnit : k % kUnit);
+      if (r >= H || c >= W) return;
       idx = int64_t(r) * W + c;
     } else {
       idx = first + it;
@@ -1883,7 +1959,7 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
         if (prm.UB)
           for (int e = lane; e < Q * r_b; e += 64) prm.UB[idx * Q * r_b + e] = cz();
       }
-      continue;
+      return;
     }
     // window origin as a sample index (x and the split planes share the layout)
     const int64_t win = (int64_t(r) * W + c) * Q + prm.st_min;
@@ -1891,8 +1967,9 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
     // ---------------------------------------------------------------- a2 SCM
     // (the FP64-solve paths are bound by their solves, not by the covariance
     // MFMAs, so they always take the full sum: no sliding-window residue)
-    const int mv = tiled_move(first + it, H, W, kChainNarrow);
-    const bool slide = PREC == 0 && MODE == kModeRun && left_ok && mv >= 0 && prm.nadd[0] >= 0;
+    static_assert(kChainNarrow == kUnit * kUnit, "a narrow chain is one unit");
+    const int mv = k % kUnit == 0 ? kMoveDown : (k / kUnit & 1) ? kMoveLeft : kMoveRight;   // tiled_move in a unit
+    const bool slide = PREC == 0 && MODE == kModeRun && left_ok && k > 0 && prm.nadd[0] >= 0;
     if constexpr (PREC != 1 && kSplitCov<P, Q>) {
       if (slide) {
         if constexpr (!kKeepAcc<P, Q>) split_reload<P, Q>(sS, n, acc);
@@ -1903,7 +1980,6 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
       scm_split<P, Q, MODE == kModeProbe ? 3 : 1>(prm.x + win, plane, prm.rec_bytes,
                                                   slide ? sDelta + mv * kDeltaList : sOffB, slide ? prm.nadd[mv] : n,
                                                   slide ? prm.nadd[mv] + prm.nrem[mv] : n, loff, acc);
-      split_store<P, Q>(acc, n, sS);
     } else if constexpr (PREC != 1) {
       SSums<P> ss{};   // gathered for the Doppler bank kernels only
       if (slide)
@@ -1912,20 +1988,20 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
       else
         scm_fp32<P, Q>(prm.x + win, plane, prm.rec_bytes, sOffB, loff, n, sS, reinterpret_cast<float*>(sBT), ss);
     } else {
-      scm_bf16x3<P, Q>(prm.xs + win, prm.xs + P * plane + win, plane, prm.rec_bytes / 2, sOffB, loff, n, sS);
+      scm_bf16x3<P, Q>(prm.xs + win, prm.xs + P * plane + win, plane, prm.rec_bytes / 2, sOffB, loff, n, acc);
     }
 
     // -------------------------------------- this pixel's slots, from S in LDS
     float v[NSL][P * P][C];
+    // the entries of block row i
+    auto slots_row = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < NSL; ++t) {
-      const bool last = t == NSL - 1;   // the diagonal slots are a lane's last
-#pragma unroll
-      for (int i = 0; i < P; ++i) {
-        const float2 s1 = sS[sblk<P, Q>(i, i) + so1[t]];
+      for (int t = 0; t < NSL; ++t) {
+        const bool last = t == NSL - 1;   // the diagonal slots are a lane's last
+        const float2 s1 = sS[lblk<P, Q>(i, i) + so1[t]];
         float y = s1.y;
         if (last) {
-          const float2 s2 = sS[sblk<P, Q>(i, i) + so2[t]];
+          const float2 s2 = sS[lblk<P, Q>(i, i) + so2[t]];
           y = diag ? s2.x : y;
         }
         if constexpr (C == 2) {
@@ -1936,7 +2012,7 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
         }
 #pragma unroll
         for (int j = i + 1; j < P; ++j) {
-          const float2 s = sS[sblk<P, Q>(i, j) + so1[t]], u = sS[sblk<P, Q>(i, j) + so2[t]];
+          const float2 s = sS[lblk<P, Q>(i, j) + so1[t]], u = sS[lblk<P, Q>(i, j) + so2[t]];
           float ux = s.x + u.x, uy = s.y - u.y, vx = s.y + u.y, vy = u.x - s.x;
           if (last) {
             ux = diag ? 2.f * s.x : ux;
@@ -1955,6 +2031,21 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
           }
         }
       }
+    };
+    if constexpr (kPhased<P, Q>) {
+      split_store<P, Q>(acc, n, sS, 0, 1);
+      slots_row(0);
+      wave_sync();
+      split_store<P, Q>(acc, n, sS, 1, SplitAcc<P, Q>::NB);
+#pragma unroll
+      for (int i = 1; i < P; ++i) slots_row(i);
+    } else {
+      if constexpr (kSplitCov<P, Q>) split_store<P, Q>(acc, n, sS, 0, SplitAcc<P, Q>::NB);
+#pragma unroll
+      for (int i = 0; i < P; ++i) slots_row(i);
+    }
+#pragma unroll
+    for (int t = 0; t < NSL; ++t) {
       if (NS % 64 != 0 && !(lane + 64 * t < NS * (2 / C))) {   // no such slot
 #pragma unroll
         for (int e = 0; e < P * P; ++e)
@@ -2248,50 +2339,44 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
     ua_ok = !zero && !bad;
 
     // ------------------------------------------ enqueue for the batched tail
-    // A full queue, or (warm tail) one that holds another chain's pixels,
-    // runs its batch here, before this pixel joins: the queued pixels wait in
-    // Bq and their own LDS slots, which this pixel's work does not touch, and
-    // the tail is inlined at one place in the loop.
     wave_sync();   // S is dead from here on
-    {
-      bool flush = nq == G;
-      int64_t cid = 0;
-      if constexpr (kWarmTail) {
-        cid = (first + it) / kChainNarrow;
-        flush = flush || (nq > 0 && cid != qchain);
-      }
-      if (flush) {
-        tail(nq);
-        nq = 0;
-      }
-      if constexpr (kWarmTail) qchain = cid;
-    }
-    // the Hermitian B from its slots, B[k][l] at k * BS + l, then one row per lane
-    constexpr int BS = Q + 2;   // 16-byte rows, spread over the banks
+    if constexpr (kWarmTail) qchain = (first + it) / kChainNarrow;
+    if constexpr (kQueueLds<P, Q>) {
 #pragma unroll
-    for (int t = 0; t < NSL; ++t) {
-      if (NS % 64 == 0 || lane + 64 * t < NS * (2 / C)) {
-        const bool dg = t == NSL - 1 && diag;
-        const int k1 = sk[t], l1 = sl[t];
-        if constexpr (C == 2) {
-          sBT[dg ? k1 * BS + k1 : k1 * BS + l1] = make_float2(bv[t][0], dg ? 0.f : bv[t][1]);
-          sBT[dg ? l1 * BS + l1 : l1 * BS + k1] = make_float2(dg ? bv[t][1] : bv[t][0], dg ? 0.f : -bv[t][1]);
-        } else {
-          float* const f = reinterpret_cast<float*>(sBT);
-          const int kk = comp ? l1 : k1;   // the diagonal entry of this lane
-          f[dg ? 2 * (kk * BS + kk) : 2 * (k1 * BS + l1) + comp] = bv[t][0];
-          f[dg ? 2 * (kk * BS + kk) + 1 : 2 * (l1 * BS + k1) + comp] = dg ? 0.f : (comp ? -bv[t][0] : bv[t][0]);
+      for (int t = 0; t < NSL; ++t) {
+        if (NS % 64 == 0 || lane + 64 * t < NS * (2 / C)) {
+          if constexpr (C == 2) sQB[nq * NS + lane + 64 * t] = make_float2(bv[t][0], bv[t][1]);
+          else reinterpret_cast<float*>(sQB)[2 * (nq * NS + (lane & 31)) + comp] = bv[t][0];
         }
       }
-    }
-    wave_sync();
-    if (tg == nq && tk < Q) {
-      const float4* const row = reinterpret_cast<const float4*>(sBT + tk * BS);
+    } else {
+      // the Hermitian B from its slots, B[k][l] at k * BS + l, then one row per lane
+      constexpr int BS = Q + 2;   // 16-byte rows, spread over the banks
 #pragma unroll
-      for (int l = 0; l < Q / 2; ++l) {
-        const float4 two = row[l];
-        Bq[2 * l] = make_float2(two.x, two.y);
-        Bq[2 * l + 1] = make_float2(two.z, two.w);
+      for (int t = 0; t < NSL; ++t) {
+        if (NS % 64 == 0 || lane + 64 * t < NS * (2 / C)) {
+          const bool dg = t == NSL - 1 && diag;
+          const int k1 = sk[t], l1 = sl[t];
+          if constexpr (C == 2) {
+            sBT[dg ? k1 * BS + k1 : k1 * BS + l1] = make_float2(bv[t][0], dg ? 0.f : bv[t][1]);
+            sBT[dg ? l1 * BS + l1 : l1 * BS + k1] = make_float2(dg ? bv[t][1] : bv[t][0], dg ? 0.f : -bv[t][1]);
+          } else {
+            float* const f = reinterpret_cast<float*>(sBT);
+            const int kk = comp ? l1 : k1;   // the diagonal entry of this lane
+            f[dg ? 2 * (kk * BS + kk) : 2 * (k1 * BS + l1) + comp] = bv[t][0];
+            f[dg ? 2 * (kk * BS + kk) + 1 : 2 * (l1 * BS + k1) + comp] = dg ? 0.f : (comp ? -bv[t][0] : bv[t][0]);
+          }
+        }
+      }
+      wave_sync();
+      if (tg == nq && tk < Q) {
+        const float4* const row = reinterpret_cast<const float4*>(sBT + tk * BS);
+#pragma unroll
+        for (int l = 0; l < Q / 2; ++l) {
+          const float4 two = row[l];
+          Bq[2 * l] = make_float2(two.x, two.y);
+          Bq[2 * l + 1] = make_float2(two.z, two.w);
+        }
       }
     }
     if (lane == 0) {
@@ -2312,8 +2397,18 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
     }
     wave_sync();
     ++nq;
+  };
+
+  // one call site each for the pixel body and the tail, which runs when the
+  // queue is full, at the end of a chain (warm tail) and at the end of the run
+  for (int64_t it = 0; it < count; ++it) {
+    pixel(it);
+    const bool end = it + 1 == count || (kWarmTail && (first + it + 1) % kChainNarrow == 0);
+    if (nq == G || (end && nq > 0)) {
+      tail(nq);
+      nq = 0;
+    }
   }
-  if (nq > 0) tail(nq);
 }
 
 }  // namespace
