@@ -2504,9 +2504,14 @@ __global__ __launch_bounds__(64, 2) void kstap_persistent(const KParams* __restr
 // it outlives the pixel: in run mode every pixel of a sliding-window chain
 // but the first starts from the previous pixel's n*S (a one-pixel move) and
 // stages only the training vectors that enter the stencil (added) and leave
-// it (subtracted), as the narrow FP32 kernels do.  LR-Kron sweeps run over all 512 lanes with the
-// block sums reduced across waves through LDS; the small factor-A solves are
-// computed identically by every wave.  The Hermitian time factors are queued
+// it (subtracted), as the narrow FP32 kernels do.  LR-Kron runs on the
+// Hermitian half of S (Slots), one value of a slot per thread and held in its
+// registers: per iteration one FP64 pass (residual and new b), one barrier for
+// the P^2 sums of R conj(b) over the waves, EIG_{r_a} on wave 0 and one
+// barrier for A.  Sweeps over all blocks of S in LDS, with a pass of their own
+// for the block sums and four barriers, took the 512 x 512, p = 5, q = 24,
+// n = 256 frame 44.4 ms (FP32) and this 30.4 ms; p = 6, q = 16 in two passes
+// at 256 x 256 14.6 -> 9.9 ms.  The Hermitian time factors are queued
 // in LDS and the batched tail (a6 + a8) runs 64/q' pixels per wave on waves
 // 0-3 at once.  Eight waves (two per SIMD, the LDS footprint allows one
 // workgroup per compute unit) hide each other's LDS, reduction and barrier
@@ -2542,9 +2547,7 @@ struct WideLds {
   static constexpr size_t oRed = oQidx + sizeof(int64_t) * NQ;       // float[kWideWaves][KRED]
   static constexpr int KRED = 2 * P * P + 8;
   static constexpr size_t oA = oRed + sizeof(float) * kWideWaves * KRED;   // float2[P*P]
-  static constexpr size_t oAp = oA + sizeof(float2) * P * P;         // float2[P*P]: block sums (A_0, R b*)
-  static constexpr size_t oB = oAp + sizeof(float2) * P * P;         // float2[Q*Q]: current b
-  static constexpr size_t oOff = oB + sizeof(float2) * Q * Q;        // int[kMaxN]
+  static constexpr size_t oOff = oA + sizeof(float2) * P * P;        // int[kMaxN]
   static constexpr size_t oDel = oOff + sizeof(int) * kMaxN;         // int[3][2*kMaxDelta]: per move, entering, leaving
   static constexpr size_t oQflag = oDel + sizeof(int) * 6 * kMaxDelta;   // int[NQ]
   static constexpr size_t oQit = oQflag + sizeof(int) * NQ;          // int[NQ]
@@ -2555,19 +2558,6 @@ struct WideLds {
 
 __device__ __forceinline__ void block_sync() { __syncthreads(); }
 
-// Sums a double over the lanes of the workgroup (every lane gets the sum).
-__device__ __forceinline__ double block_sumd(double v, double* red) {
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  v = wsumd(v);
-  if (lane == 0) red[w] = v;
-  block_sync();
-  v = 0.0;
-#pragma unroll
-  for (int i = 0; i < kWideWaves; ++i) v += red[i];
-  block_sync();
-  return v;
-}
-
 template <int P, int Q, int RBM, int MODE, int PREC, bool VAR = false>
 __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t first, int64_t count, char* lds) {
   using EC = typename Pick<PREC == 1, double2, float2>::type;
@@ -2577,7 +2567,7 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
   constexpr int NB = L::NB;
   constexpr int QS = Q + 1;
   constexpr int QQ = Q * Q;
-  constexpr int NE = (QQ + kWideThreads - 1) / kWideThreads;   // q x q entries per lane
+  constexpr int NDT = (QQ + kWideThreads - 1) / kWideThreads;   // dimensions of b per thread
   constexpr int RAM = L::RAM;
   constexpr int NPAIR = NB * (NB + 1) / 2;
   constexpr int MYP = (NPAIR + kWideWaves - 1) / kWideWaves;   // tile pairs per wave (round-robin)
@@ -2592,8 +2582,6 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
   EC* const sUA = reinterpret_cast<EC*>(lds + L::oUA);
   EC* const sAh = reinterpret_cast<EC*>(lds + L::oAh);
   float2* const sA = reinterpret_cast<float2*>(lds + L::oA);
-  float2* const sAp = reinterpret_cast<float2*>(lds + L::oAp);
-  float2* const sB = reinterpret_cast<float2*>(lds + L::oB);
   int* const sOff = reinterpret_cast<int*>(lds + L::oOff);
   int* const sDel = reinterpret_cast<int*>(lds + L::oDel);
   float2* const sHq = reinterpret_cast<float2*>(lds + L::oHq);
@@ -2605,7 +2593,6 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
 
   // the wave index is uniform: keep it (and the tile pairs below) in SGPRs
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  constexpr int NL = (QQ + 63) / 64;   // q x q block entries per lane in the block passes
   const int n = prm.n, H = prm.H, W = prm.W;
   const int r_a = prm.r_a, r_b = prm.r_b;
 
@@ -2867,308 +2854,275 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
     }
     block_sync();
 
-    // S(i,j)[k][l] for any (i, j)
-    auto Sget = [&](int i, int j, int k, int l) __attribute__((always_inline)) -> float2 {
-      if (i <= j) return sS[((i * P - i * (i - 1) / 2 + (j - i)) * Q + k) * QS + l];
-      return cconj(sS[((j * P - j * (j - 1) / 2 + (i - j)) * Q + l) * QS + k]);
-    };
-
-    // Block pass: out[ij] = scale * sum_kl conj(w_kl) S(i,j)_kl for the P*P
-    // blocks, dealt round-robin to the waves; a wave's lanes split the q x q
-    // entries (this lane: e = lane + 64 m, weight wv[m]) and reduce with DPP.
-    // Optionally accumulates sum |S(i,j)_kl|^2 of the visited entries in *nr.
-    // out[] is complete after the next block_sync.
-    // The wave's blocks are accumulated first and reduced together, so the
-    // DPP reduction chains of different blocks overlap.
-    auto block_pass = [&](const float2 (&wv)[NL], float scale, float2* out, double* nr) {
-      constexpr int NU = (P * P + kWideWaves - 1) / kWideWaves;
-      float2 acc[NU];
-      double n2 = 0.0;   // exact squares of the FP32 entries, FP64 sums
+    // ------------------------- this thread's dimensions of b (Slots), from S
+    // Thread e + 512 t holds value x (e < q^2 / 2) or y of one slot.  Rotating
+    // the y threads' entries by -j (rot) gives both the same sums.
+    float v[NDT][P * P], wgt[NDT], one[NDT];   // values, weight, and the all-ones b
+    int kb[NDT], lb[NDT], comp[NDT];
+    bool dgl[NDT], has[NDT];
 #pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        acc[u] = cz();
-        const int ij = wave + kWideWaves * u;
-        if (ij < P * P) {   // uniform per wave
-          const int i = ij / P, j = ij - (ij / P) * P;
-          const bool up = i <= j;
-          const int a = up ? i : j, b = up ? j : i;
-          const int base = (a * P - a * (a - 1) / 2 + (b - a)) * Q * QS;
+    for (int t = 0; t < NDT; ++t) {
+      const int e = tid + kWideThreads * t;
+      has[t] = e < QQ;
+      comp[t] = e >= QQ / 2 && has[t] ? 1 : 0;
+      const int s = has[t] ? e - comp[t] * (QQ / 2) : 0;
+      const int d = s / Q + 1, k = s - (d - 1) * Q;
+      dgl[t] = d == Q / 2 && k >= Q / 2;
+      kb[t] = dgl[t] ? k - Q / 2 : k;
+      lb[t] = dgl[t] ? k : (k + d >= Q ? k + d - Q : k + d);
+      wgt[t] = !has[t] ? 0.f : dgl[t] ? 1.f : 2.f;
+      one[t] = (comp[t] && !dgl[t]) ? 0.f : 1.f;
+      const int dk = comp[t] ? lb[t] : kb[t];   // the diagonal entry of this thread
+      const int o1 = dgl[t] ? dk * QS + dk : kb[t] * QS + lb[t];
+      const int o2 = dgl[t] ? o1 : lb[t] * QS + kb[t];
+      const bool rot = comp[t] && !dgl[t];
+      if (wave * 64 + kWideThreads * t < QQ) {   // uniform: some lane of this wavefront has one
 #pragma unroll
-          for (int m = 0; m < NL; ++m) {
-            if (lane + 64 * m < QQ) {
-              const int e = lane + 64 * m;
-              int k = e / Q, l = e - (e / Q) * Q;
-              asm volatile("" : "+v"(k), "+v"(l));
-              float2 sv = sS[base + (up ? k * QS + l : l * QS + k)];
-              sv.y = up ? sv.y : -sv.y;
-              acc[u] = ccfma(wv[m], sv, acc[u]);
-              if (nr) n2 = fma(double(sv.x), double(sv.x), fma(double(sv.y), double(sv.y), n2));
-            }
+        for (int i = 0; i < P; ++i) {
+          const float2 s1 = sS[sblk<P, Q>(i, i) + o1];
+          v[t][i] = rot ? s1.y : s1.x;
+#pragma unroll
+          for (int j = i + 1; j < P; ++j) {
+            const float2 a = sS[sblk<P, Q>(i, j) + o1], u = sS[sblk<P, Q>(i, j) + o2];
+            v[t][hoff<P>(i, j)] = rot ? a.y - u.y : a.x + u.x;
+            v[t][hoff<P>(i, j) + 1] = rot ? u.x - a.x : a.y + u.y;
           }
         }
-      }
-      if (nr) *nr += n2;
-      {
-        constexpr int NS = (2 * NU + 3) / 4 * 4;
-        float sums[NS];
+      } else {
 #pragma unroll
-        for (int f = 0; f < NS; ++f) sums[f] = (f < 2 * NU) ? ((f & 1) ? acc[f / 2].y : acc[f / 2].x) : 0.f;
-        wsum_n<NS>(sums);
-#pragma unroll
-        for (int u = 0; u < NU; ++u) acc[u] = make_float2(sums[2 * u], sums[2 * u + 1]);
+        for (int e2 = 0; e2 < P * P; ++e2) v[t][e2] = 0.f;
       }
+    }
+    // Partial sums of R conj(b) (given w b) and of `extra` over this
+    // wavefront, to red; rr (FP64) to redd
+    constexpr int NR = (P * P + 1 + 3) / 4 * 4;
+    constexpr int NACT = (QQ + 63) / 64 < kWideWaves ? (QQ + 63) / 64 : kWideWaves;   // wavefronts with dimensions
+    auto publish = [&](const float (&wb)[NDT], float extra, double rr) __attribute__((always_inline)) {
+      if (wave < NACT) {
+        float sums[NR];
 #pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        const int ij = wave + kWideWaves * u;
-        if (ij < P * P && lane == 0) out[ij] = cscale(acc[u], scale);
+        for (int e = 0; e < NR; ++e) sums[e] = (e == P * P) ? extra : 0.f;
+#pragma unroll
+        for (int t = 0; t < NDT; ++t) {
+          if (t > 0 && wave * 64 + kWideThreads * t >= QQ) continue;   // uniform
+#pragma unroll
+          for (int e = 0; e < P * P; ++e) sums[e] = fmaf(v[t][e], wb[t], sums[e]);
+        }
+        wsum_n<NR>(sums);
+        rr = wsumd(rr);
+        if (lane == 0) {
+#pragma unroll
+          for (int e = 0; e <= P * P; ++e) red[wave * L::KRED + e] = sums[e];
+          redd[wave] = rr;
+        }
       }
+      block_sync();
+    };
+    // the sum over the wavefronts of entry e <= P*P (R conj(b): P*P reals)
+    auto total = [&](int e) __attribute__((always_inline)) -> float {
+      float s = 0.f;
+#pragma unroll
+      for (int w = 0; w < NACT; ++w) s += red[w * L::KRED + e];
+      return e < P ? s : e < P * P ? 0.5f * s : s;
+    };
+    auto totald = [&]() __attribute__((always_inline)) -> double {
+      double s = 0.0;
+#pragma unroll
+      for (int w = 0; w < NACT; ++w) s += redd[w];
+      return s;
     };
 
     // ------------------------------------------------ a4 init, ||R||_F = ||S||_F
-    // The current space factor A lives in LDS (sA, P x P): every lane reads
-    // it, as broadcasts, in the sweeps.
+    // The space factor A is P*P reals (hoff) in LDS (sA), copied to registers
+    // by every thread for a sweep.
+    float* const sAr = reinterpret_cast<float*>(sA);
+    float A[P * P], anorm2;
+    auto load_a = [&]() __attribute__((always_inline)) {
+      float nd = 0.f, no = 0.f;
+#pragma unroll
+      for (int e = 0; e < P * P; ++e) {
+        A[e] = sAr[e];
+        if (e < P) nd = fmaf(A[e], A[e], nd);
+        else no = fmaf(A[e], A[e], no);
+      }
+      anorm2 = fmaf(2.f, no, nd);
+    };
     double normR2;
     {
-      float2 wv[NL];
+      double nr = 0.0;   // exact squares of the FP32 entries, FP64 sums
+      float wb[NDT];
 #pragma unroll
-      for (int m = 0; m < NL; ++m) wv[m] = make_float2(1.f, 0.f);
-      double nr = 0.0;
-      block_pass(wv, 1.f / float(QQ), sAp, &nr);
-      normR2 = block_sumd(nr, redd);   // its barriers also publish sAp
-      float an = 0.f;
+      for (int t = 0; t < NDT; ++t) {
+        double nd = 0.0, no = 0.0;
 #pragma unroll
-      for (int e = 0; e < P * P; ++e) an += cabs2(sAp[e]);
-      if (double(an) <= 1e-24 * normR2) {   // fallback: partial trace R vec(I_q)
-#pragma unroll
-        for (int m = 0; m < NL; ++m) {
-          const int e = lane + 64 * m;
-          wv[m] = (e < QQ && e / Q == e - (e / Q) * Q) ? make_float2(1.f, 0.f) : cz();
+        for (int e = 0; e < P * P; ++e) {
+          const double x = v[t][e];
+          if (e < P) nd = fma(x, x, nd);
+          else no = fma(x, x, no);
         }
-        block_sync();
-        block_pass(wv, 1.f, sAp, nullptr);
-        block_sync();
+        nr = fma(double(wgt[t]), fma(0.5, no, nd), nr);
+        wb[t] = wgt[t] * one[t];
       }
-      if (tid < P * P) sA[tid] = sAp[tid];
+      publish(wb, 0.f, nr);
+      normR2 = totald();
+      if (tid < P * P) sAr[tid] = total(tid) * (1.f / float(QQ));
       block_sync();
+      load_a();
+      if (double(anorm2) <= 1e-24 * normR2) {   // fallback: partial trace R vec(I_q) (uniform)
+#pragma unroll
+        for (int t = 0; t < NDT; ++t) wb[t] = (has[t] && dgl[t]) ? 1.f : 0.f;
+        publish(wb, 0.f, 0.0);
+        if (tid < P * P) sAr[tid] = total(tid);
+        block_sync();
+        load_a();
+      }
     }
 
     float eta = 0.f;
     int iters = 0;
     const bool zero = !(normR2 > 0.0);
     const bool bad = !isfinite(normR2);
-    float2 bv[NE];
+    float bv[NDT];
 #pragma unroll
-    for (int t = 0; t < NE; ++t) bv[t] = cz();
+    for (int t = 0; t < NDT; ++t) bv[t] = 0.f;
     EC ua[P];
 #pragma unroll
     for (int i = 0; i < P; ++i) ua[i] = warm ? sUA[i * RAM] : czero<EC>();
 
     if (!zero && !bad) {
-      double resid = 0.0;
-      float anorm2 = 0.f;
-#pragma unroll
-      for (int e = 0; e < P * P; ++e) anorm2 += cabs2(sA[e]);
-      // One LR-Kron half-step pair: the new b = R^T conj(a) / ||a||^2
-      // (lane-owned entries, all blocks), then the block pass R conj(b) /
-      // ||b||^2 into sAp.  If RES also the residual of (A, b) by the expansion
-      // ||R||^2 - 2 Re(a^H R conj(b)) + ||a||^2 ||b||^2, every term summed in
-      // FP64 from the FP32 entries (each product exact), so the expansion
-      // keeps the residual where it is small.
-      auto sweep = [&](bool res) __attribute__((always_inline)) {
-        const float ainv = xrcp(anorm2);
-        double rr = 0.0, xr = 0.0, b2 = 0.0, a2 = 0.0;
-        float bb = 0.f;
-        if (res) {
-#pragma unroll
-          for (int e = 0; e < P * P; ++e) {
-            const float2 ae = sA[e];
-            a2 = fma(double(ae.x), double(ae.x), fma(double(ae.y), double(ae.y), a2));
-          }
-        }
-#pragma unroll
-        for (int t = 0; t < NE; ++t) {
-          const int e = tid + kWideThreads * t;
-          if (e < QQ) {
-            // opaque indices: the P^2 entry addresses are formed here, per
-            // sweep, not hoisted out of the iteration loop into registers
-            int k = e / Q, l = e - (e / Q) * Q;
-            asm volatile("" : "+v"(k), "+v"(l));
-            float2 bn = cz();
-            if (res) {
-              // one partial sum per block row: P independent FMA chains
-              double px[P], py[P];
-#pragma unroll
-              for (int i = 0; i < P; ++i) {
-                px[i] = 0.0;
-                py[i] = 0.0;
-#pragma unroll
-                for (int j = 0; j < P; ++j) {
-                  const float2 sv = Sget(i, j, k, l);
-                  const float2 aij = sA[i * P + j];
-                  const double ax = aij.x, ay = aij.y, sx = sv.x, sy = sv.y;
-                  px[i] = fma(ax, sx, fma(ay, sy, px[i]));
-                  py[i] = fma(ax, sy, fma(-ay, sx, py[i]));
-                }
-              }
-              double gx = 0.0, gy = 0.0;
-#pragma unroll
-              for (int i = 0; i < P; ++i) {
-                gx += px[i];
-                gy += py[i];
-              }
-              const double bx = bv[t].x, by = bv[t].y;
-              xr = fma(bx, gx, fma(by, gy, xr));
-              b2 = fma(bx, bx, fma(by, by, b2));
-              bn = make_float2(float(gx) * ainv, float(gy) * ainv);
-            } else {
-              float2 pb[P];
-#pragma unroll
-              for (int i = 0; i < P; ++i) {
-                pb[i] = cz();
-#pragma unroll
-                for (int j = 0; j < P; ++j) pb[i] = ccfma(sA[i * P + j], Sget(i, j, k, l), pb[i]);
-              }
-#pragma unroll
-              for (int i = 0; i < P; ++i) bn = cadd(bn, pb[i]);
-              bn = cscale(bn, ainv);
-            }
-            bv[t] = bn;
-            bb += cabs2(bn);
-            sB[e] = bn;
-          } else {
-            bv[t] = cz();
-          }
-        }
-        if (res) rr = fma(b2, a2, -2.0 * xr);
-        // both sums through one barrier (which also publishes sB); red and
-        // redd are next written after the barrier that ends this sweep
-        bb = wsum(bb);
-        if (res) rr = wsumd(rr);
-        if (lane == 0) {
-          red[wave] = bb;
-          redd[wave] = rr;
-        }
-        block_sync();
-        float bsum = 0.f;
-        double rsum = 0.0;
-#pragma unroll
-        for (int i = 0; i < kWideWaves; ++i) {
-          bsum += red[i];
-          rsum += redd[i];
-        }
-        if (res) resid = fmax(normR2 + rsum, 0.0);
-        float2 wv[NL];
-#pragma unroll
-        for (int m = 0; m < NL; ++m) wv[m] = (lane + 64 * m < QQ) ? sB[lane + 64 * m] : cz();
-        block_pass(wv, 1.f / bsum, sAp, nullptr);
-        block_sync();
-      };
-      // EIG_{r_a} of Herm(A'), A' = sAp
+      // EIG_{r_a} of A' = R conj(b) / ||b||^2 on wave 0 (the sums over the
+      // wavefronts are in red), which writes A to sA
       auto eig_a = [&](bool cold) __attribute__((always_inline)) {
-        if (tid < P * P) {
-          const int i = tid / P, j = tid - (tid / P) * P;
-          const EC h = cscale(cadd(cto<EC>(sAp[i * P + j]), cconj(cto<EC>(sAp[j * P + i]))), ES(0.5));
-          sAh[tid] = h;
-        }
-        block_sync();
+        if (wave != 0) return;
+        const float mine = total(lane <= P * P ? lane : P * P);
+        const float binv = 1.f / __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine), P * P));
         if (r_a == 1) {
-          // wave 0 alone: the iteration is the same on every lane, so the
-          // other waves would only take SIMD issue slots from it
-          if (wave == 0) {
-            if constexpr (PREC == 0) {   // the factor in registers for the iteration (FP32 fits the budget)
-              EC mh[P * P];
+          ES h[P * P], lam;
 #pragma unroll
-              for (int e = 0; e < P * P; ++e) mh[e] = sAh[e];
-              power_top<P, EC>([&](int i, int j) { return mh[i * P + j]; }, ua, cold, 500, 2e-6);
-            } else {
-              power_top<P, EC>([&](int i, int j) { return sAh[i * P + j]; }, ua, cold, 500, 1e-12);
-            }
-            ES lam = 0;
+          for (int e = 0; e < P * P; ++e)
+            h[e] = ES(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine), e)) * binv);
+          power_top_h<P, EC, ES>(h, ua, cold, 500, PREC == 1 ? 1e-12 : 2e-6, &lam);
+          if (lane == 0) {
 #pragma unroll
             for (int i = 0; i < P; ++i) {
-              EC s = czero<EC>();
+              sAr[i] = float(lam * cabs2(ua[i]));
 #pragma unroll
-              for (int j = 0; j < P; ++j) s = cfma(sAh[i * P + j], ua[j], s);
-              lam += ua[i].x * s.x + ua[i].y * s.y;
+              for (int j = i + 1; j < P; ++j) {
+                const EC c2 = cmul(ua[i], cconj(ua[j]));
+                sAr[hoff<P>(i, j)] = float(lam * c2.x);
+                sAr[hoff<P>(i, j) + 1] = float(lam * c2.y);
+              }
             }
-#pragma unroll
-            for (int i = 0; i < P; ++i)
-#pragma unroll
-              for (int j = 0; j < P; ++j)
-                if (lane == i * P + j) sA[i * P + j] = tof(cscale(cmul(ua[i], cconj(ua[j])), lam));
           }
-          block_sync();   // publishes sA; sAh is rewritten by the next call
-          anorm2 = 0.f;
-#pragma unroll
-          for (int e = 0; e < P * P; ++e) anorm2 += cabs2(sA[e]);
           return;
         }
-        // r_a > 1: wave 0 runs the subspace iteration with lane k holding row
-        // k of Herm(A') and of the basis (dot products by wave reductions),
-        // warm-started from the previous U_A; then Hs = U^H Herm(A') U
-        // (r_a x r_a) to LDS.  Every thread then forms A = U Hs U^H, with
-        // ||A||^2 = ||Hs||_F^2.  The sweep's reduction area is free here and
-        // holds the basis exchange and Hs.
-        EC* const sVs = reinterpret_cast<EC*>(red);   // [RAM][P] basis exchange
-        EC* const sHs = sVs + RAM * P;                 // [RAM][RAM]
-        if (wave == 0) {
-          const bool rowk = lane < P;
-          float2 mrow[P];
-#pragma unroll
-          for (int j = 0; j < P; ++j) mrow[j] = tof(sAh[(rowk ? lane : 0) * P + j]);
-          EC va[RAM];
-#pragma unroll
-          for (int c = 0; c < RAM; ++c) va[c] = (!cold && rowk) ? sUA[lane * RAM + c] : czero<EC>();
-          group_subspace<RAM, 64, P, EC, true>(mrow, rowk, r_a, va, sVs, cold, 500, PREC ? 1e-12 : 2e-6);
-          small::lane_sync();
-          if (rowk) {
-#pragma unroll
-            for (int c = 0; c < RAM; ++c)
-              if (c < r_a) sUA[lane * RAM + c] = va[c];
-          }
-          small::lane_sync();
-          // (Herm(A') U)[k][b] on lane k, then Hs[a][b] = sum_k conj(U[k][a]) (Herm(A') U)[k][b]
-          EC au[RAM];
-#pragma unroll
-          for (int b = 0; b < RAM; ++b) {
-            au[b] = czero<EC>();
-            if (b < r_a && rowk) {
-#pragma unroll
-              for (int j = 0; j < P; ++j) au[b] = cfma(sAh[lane * P + j], sUA[j * RAM + b], au[b]);
-            }
-          }
-#pragma unroll
-          for (int a2 = 0; a2 < RAM; ++a2)
-#pragma unroll
-            for (int b = 0; b < RAM; ++b)
-              if (a2 < r_a && b < r_a) {
-                const EC hs = gsum<64>(rowk ? ccfma(va[a2], au[b], czero<EC>()) : czero<EC>());
-                if (lane == 0) sHs[a2 * RAM + b] = hs;
-              }
+        // r_a > 1: subspace iteration with lane k holding row k of A' and of
+        // the basis (dot products by wave reductions), warm-started from the
+        // previous U_A; then Hs = U^H A' U (r_a x r_a) and A = U Hs U^H, entry
+        // (i, j) on lane i P + j
+        EC* const sVs = reinterpret_cast<EC*>(stage);   // [RAM][P] basis exchange (the staging area is free)
+        EC* const sHs = sVs + RAM * P;                  // [RAM][RAM]
+        if (lane < P * P) sAr[lane] = mine * binv;
+        lane_sync();
+        const int ai = lane / P, aj = lane - (lane / P) * P;
+        if (lane < P * P) {
+          const int lo = ai < aj ? ai : aj, hi = ai < aj ? aj : ai;
+          EC h;
+          h.x = ai == aj ? sAr[ai] : sAr[hoff<P>(lo, hi)];
+          h.y = ai == aj ? 0.f : ai < aj ? sAr[hoff<P>(lo, hi) + 1] : -sAr[hoff<P>(lo, hi) + 1];
+          sAh[lane] = h;
         }
-        block_sync();
-        anorm2 = 0.f;
-        for (int a2 = 0; a2 < r_a; ++a2)
-          for (int b = 0; b < r_a; ++b) anorm2 += float(cabs2(sHs[a2 * RAM + b]));
-        if (tid < P * P) {
-          const int ai = tid / P, aj = tid - (tid / P) * P;
-          EC acc = czero<EC>();
+        lane_sync();
+        const bool rowk = lane < P;
+        float2 mrow[P];
+#pragma unroll
+        for (int j = 0; j < P; ++j) mrow[j] = tof(sAh[(rowk ? lane : 0) * P + j]);
+        EC va[RAM];
+#pragma unroll
+        for (int c = 0; c < RAM; ++c) va[c] = (!cold && rowk) ? sUA[lane * RAM + c] : czero<EC>();
+        group_subspace<RAM, 64, P, EC, true>(mrow, rowk, r_a, va, sVs, cold, 500, PREC ? 1e-12 : 2e-6);
+        lane_sync();
+        if (rowk) {
+#pragma unroll
+          for (int c = 0; c < RAM; ++c)
+            if (c < r_a) sUA[lane * RAM + c] = va[c];
+        }
+        lane_sync();
+        // (A' U)[k][b] on lane k, then Hs[a][b] = sum_k conj(U[k][a]) (A' U)[k][b]
+        EC au[RAM];
+#pragma unroll
+        for (int b = 0; b < RAM; ++b) {
+          au[b] = czero<EC>();
+          if (b < r_a && rowk) {
+#pragma unroll
+            for (int j = 0; j < P; ++j) au[b] = cfma(sAh[lane * P + j], sUA[j * RAM + b], au[b]);
+          }
+        }
+#pragma unroll
+        for (int a2 = 0; a2 < RAM; ++a2)
+#pragma unroll
+          for (int b = 0; b < RAM; ++b)
+            if (a2 < r_a && b < r_a) {
+              const EC hs = gsum<64>(rowk ? ccfma(va[a2], au[b], czero<EC>()) : czero<EC>());
+              if (lane == 0) sHs[a2 * RAM + b] = hs;
+            }
+        lane_sync();
+        if (lane < P * P && ai <= aj) {
+          EC acc2 = czero<EC>();
           for (int a2 = 0; a2 < r_a; ++a2) {
             EC t2 = czero<EC>();
             for (int b = 0; b < r_a; ++b) t2 = cfma(sHs[a2 * RAM + b], cconj(sUA[aj * RAM + b]), t2);
-            acc = cfma(sUA[ai * RAM + a2], t2, acc);
+            acc2 = cfma(sUA[ai * RAM + a2], t2, acc2);
           }
-          sA[tid] = tof(acc);
+          if (ai == aj) {
+            sAr[ai] = float(acc2.x);
+          } else {
+            sAr[hoff<P>(ai, aj)] = float(acc2.x);
+            sAr[hoff<P>(ai, aj) + 1] = float(acc2.y);
+          }
         }
-        block_sync();   // publishes sA; the reduction area is free again
       };
-      // sweep 0 has no residual; after sweep k >= 1 the stop rule looks at
-      // eta_k (one call site per lambda keeps the code, and its registers, small)
+      // Iteration k: the residual of (A, b) in FP64 (k > 0), the new b, and
+      // the partial sums of R conj(b), through one barrier; then the stop rule
+      // on every thread and EIG_{r_a} on wave 0.
       double eta_prev = INFINITY;
       for (int k = 0;; ++k) {
-        sweep(k > 0);
+        const float ainv = xrcp(anorm2);
+        double rr = 0.0;
+        float wb[NDT], bb = 0.f;
+#pragma unroll
+        for (int t = 0; t < NDT; ++t) {
+          if (t > 0 && wave * 64 + kWideThreads * t >= QQ) {   // uniform
+            wb[t] = 0.f;
+            continue;
+          }
+          float bn;
+          if (k > 0) {
+            const double bd = bv[t];
+            double s = 0.0, rd = 0.0, ro = 0.0;
+#pragma unroll
+            for (int e = 0; e < P * P; ++e) {
+              const double x = v[t][e], a = A[e];
+              const double dlt = fma(e < P ? -a : -2.0 * a, bd, x);
+              if (e < P) rd = fma(dlt, dlt, rd);
+              else ro = fma(dlt, dlt, ro);
+              s = fma(a, x, s);
+            }
+            rr = fma(double(wgt[t]), fma(0.5, ro, rd), rr);
+            bn = float(s) * ainv;
+          } else {
+            float s = 0.f;
+#pragma unroll
+            for (int e = 0; e < P * P; ++e) s = fmaf(A[e], v[t][e], s);
+            bn = s * ainv;
+          }
+          bv[t] = bn;
+          wb[t] = wgt[t] * bn;
+          bb = fmaf(wb[t], bn, bb);
+        }
+        publish(wb, bb, rr);
         if (k > 0) {
-          const double e = sqrt(resid / normR2);
+          const double e = sqrt(totald() / normR2);
           eta = float(e);
           const bool stop = iters >= prm.max_iter ||
                             (prm.eps > 0.0 && iters >= prm.min_iter && fabs(e - eta_prev) <= prm.eps);
@@ -3177,6 +3131,8 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
         }
         eig_a(k == 0 && !warm);
         iters = k + 1;
+        block_sync();   // publishes sA; red and redd are free again
+        load_a();
       }
     }
     // U_A of this pixel (rows of the r_a = 1 power iterate, or the subspace)
@@ -3189,14 +3145,16 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
     ua_ok = !zero && !bad;
     block_sync();
     // ------------------------------------------ enqueue for the batched tail
-    // (sB holds the final b = R^T conj(a) / ||a||^2 of a finite pixel)
-    float2* const hq = sHq + nq * QQ;
+    // the Hermitian B from its slots
+    {
+      float* const f = reinterpret_cast<float*>(sHq + nq * QQ);
 #pragma unroll
-    for (int t = 0; t < NE; ++t) {
-      const int e = tid + kWideThreads * t;
-      if (e < QQ) {
-        const int k = e / Q, l = e - (e / Q) * Q;
-        hq[e] = cscale(cadd(sB[k * Q + l], cconj(sB[l * Q + k])), 0.5f);
+      for (int t = 0; t < NDT; ++t) {
+        if (!has[t]) continue;
+        const int dk = comp[t] ? lb[t] : kb[t];
+        f[dgl[t] ? 2 * (dk * Q + dk) : 2 * (kb[t] * Q + lb[t]) + comp[t]] = bv[t];
+        f[dgl[t] ? 2 * (dk * Q + dk) + 1 : 2 * (lb[t] * Q + kb[t]) + comp[t]] =
+            dgl[t] ? 0.f : (comp[t] ? -bv[t] : bv[t]);
       }
     }
     if (tid == 0) {

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [(2, 8, "fp32"), (2, 32, "fp32"), (3, 8, "fp32"), (3, 12, "fp32"), (3, 16, "fp32"), (4, 16, "fp32"),
           (6, 8, "fp32"), (3, 8, "bf16x3"), (3, 12, "bf16x3"), (3, 16, "bf16x3"),
-          (3, 16, "fp32_f64")]
+          (3, 16, "fp32_f64"), (5, 24, "fp32"), (6, 16, "fp32"), (5, 24, "bf16x3")]
 
 
 @pytest.mark.parametrize("p,q,precision", SHAPES)
