@@ -155,12 +155,20 @@ __device__ __forceinline__ void wsum_n(float (&v)[N]) {
     v[4 * m + 3] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, 48));
   }
 }
+// A swap or mirror that every lane takes part in (ROWS 0xF) has no lanes that
+// keep an old value, so none is set up: the zeros an update would start from
+// were two of the five instructions of every FP64 step.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double dppd(double v) {
   const int2 i = __builtin_bit_cast(int2, v);
   int2 o;
-  o.x = __builtin_amdgcn_update_dpp(0, i.x, CTRL, ROWS, 0xF, false);
-  o.y = __builtin_amdgcn_update_dpp(0, i.y, CTRL, ROWS, 0xF, false);
+  if constexpr (ROWS == 0xF) {
+    o.x = __builtin_amdgcn_mov_dpp(i.x, CTRL, ROWS, 0xF, true);
+    o.y = __builtin_amdgcn_mov_dpp(i.y, CTRL, ROWS, 0xF, true);
+  } else {
+    o.x = __builtin_amdgcn_update_dpp(0, i.x, CTRL, ROWS, 0xF, false);
+    o.y = __builtin_amdgcn_update_dpp(0, i.y, CTRL, ROWS, 0xF, false);
+  }
   return __builtin_bit_cast(double, o);
 }
 __device__ __forceinline__ double wsumd(double v) {
@@ -1732,7 +1740,7 @@ struct Lds {
   static constexpr size_t oAh = oUA + sizeof(EC) * P * RAM;               // EC[P*P]
   static constexpr size_t oQUA = oAh + sizeof(EC) * P * P;                // EC[G][P*RAM]
   static constexpr size_t oBT = (oQUA + sizeof(EC) * G * P * RAM + 15) / 16 * 16;   // kBT bytes
-  static constexpr size_t oS = (oBT + kBT + 15) / 16 * 16;                // float2[P(P+1)/2][Q][Q+1]
+  static constexpr size_t oS = (oBT + kBT + 15) / 16 * 16;                // float2[blocks][Q][Q+1]
   static constexpr size_t oA = oS + sizeof(float2) * kBlocksLds<P, Q> * Q * (Q + 1);   // float2[P*P]
   static constexpr size_t oQB = oA + sizeof(float2) * P * P;              // float2[G][NS] (kQueueLds)
   static constexpr size_t oQidx = oQB + (kQueueLds<P, Q> ? sizeof(float2) * G * Slots<P, Q>::NS : 0);   // int64[G]
@@ -1861,24 +1869,11 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
       tail_batch<P, Q, RBM, MODE, EC, false, true>(prm, Bq, tg, nfill, sQflag, sQidx, sQeta, sQit, sQUA, tail_scratch,
                                                    PREC ? 1e-10 : 2e-6, vbw, keep, ok);
     } else {
-      auto rows = [&](auto rank) __attribute__((always_inline)) {
-        tail_rows<P, Q, RBM, decltype(rank)::value, MODE, EC>(prm, Bq, nfill, sQflag, sQidx, sQeta, sQit, sQUA,
-                                                              reinterpret_cast<char*>(sBT), PREC ? 1e-10 : 2e-6, vbw,
-                                                              keep, ok);
-      };
-      // r_b as a constant (r_b > 4 takes the RBM = 8 classes)
-      if constexpr (RBM == 4) {
-        if (r_b == 4) rows(Int<4>());
-        else if (r_b == 3) rows(Int<3>());
-        else if (r_b == 2) rows(Int<2>());
-        else if (r_b == 1) rows(Int<1>());
-        else rows(Int<0>());
-      } else {
-        if (r_b == 8) rows(Int<8>());
-        else if (r_b == 7) rows(Int<7>());
-        else if (r_b == 6) rows(Int<6>());
-        else rows(Int<5>());
-      }
+      with_rank<RBM>(r_b, [&](auto rank) __attribute__((always_inline)) {
+        tail_rows<P, Q, RBM, decltype(rank)::value, MODE, EC, false>(
+            prm, Bq, 0, nfill, sQflag, sQidx, sQeta, sQit, sQUA, reinterpret_cast<char*>(sBT), PREC ? 1e-10 : 2e-6, vbw,
+            keep, ok);
+      });
     }
     if constexpr (kWarmTail) {
       bchain = qchain;
@@ -2419,6 +2414,14 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
 namespace kstap {
 namespace {
 
+// Wavefronts per SIMD that the run-mode kernels are compiled for.  The p = 3,
+// q = 8 FP32 kernel needs 172 registers on its own and nothing spills at the
+// 168 of three: 512 x 512, n = 64 877 -> 715 us.  p = 3, q = 16 needs 220: at
+// 168 it spills some 60 accesses a pixel and takes the 1024 x 1024 frame 7.9 ms
+// instead of 5.7.
+template <int P, int Q, int RBM, int PREC, bool PLAIN>
+constexpr int kWavesPerSimd = (PLAIN && PREC == 0 && P <= 3 && Q == 8 && RBM == 4) ? 3 : 2;
+
 // Which statistic a kernel is compiled for: the plain one, its variants
 // (filter, enhancement, passes), or the FP32 Doppler bank (kstap_bank.h).
 enum Variant { kPlain = 0, kVariant = 1, kBank = 2 };
@@ -2429,7 +2432,7 @@ enum Variant { kPlain = 0, kVariant = 1, kBank = 2 };
 // compiled into a kernel of their own, so that the plain statistic keeps its
 // register budget.
 template <int P, int Q, int RBM, int MODE, int PREC, int VAR = kPlain>
-__global__ __launch_bounds__(64, 2) void kstap_kernel(const KParams prm) {
+__global__ __launch_bounds__(64, (kWavesPerSimd<P, Q, RBM, PREC, VAR == kPlain && MODE == kModeRun>)) void kstap_kernel(const KParams prm) {
   constexpr bool kBankKernel = VAR == kBank && PREC == 0;
   __shared__ __attribute__((aligned(16))) char lds[kBankKernel ? BankLds<P, Q, RBM>::bytes : Lds<P, Q, RBM, PREC>::bytes];
   int64_t first, count;
@@ -2456,7 +2459,7 @@ __global__ __launch_bounds__(64, 2) void kstap_kernel(const KParams prm) {
 // device counters until every queue is empty (kQueues queues, see kstap_internal.h).  Items are numbered tile after
 // tile in the order of `order` (longest tiles first); prefix[j] is the first item of order[j] (prefix[nt] = total).
 template <int P, int Q, int RBM, int PREC>
-__global__ __launch_bounds__(64, 2) void kstap_persistent(const KParams* __restrict__ descs,
+__global__ __launch_bounds__(64, (kWavesPerSimd<P, Q, RBM, PREC, true>)) void kstap_persistent(const KParams* __restrict__ descs,
                                                           const int32_t* __restrict__ order,
                                                           const int64_t* __restrict__ prefix, int nt,
                                                           int ppb, unsigned long long* counter) {
@@ -2495,14 +2498,15 @@ __global__ __launch_bounds__(64, 2) void kstap_persistent(const KParams* __restr
 // ====================================================================
 // Wide pixels (p*q > 64): one 512-lane workgroup (8 wavefronts) per pixel.
 //
-// The covariance tiles (16 x 16, upper block-triangle) are dealt round-robin
-// to the 8 waves.  Training vectors are staged in LDS 16 at a time (split
-// BF16 hi/lo pairs for PREC 1, FP32 for PREC 0), double-buffered: the global
-// loads of the next chunk are in flight while the waves run the MFMAs of the
-// current one.  S is kept as its upper q x q blocks S(i,j), i <= j (the lower
-// blocks are their conjugate transposes), which halves its LDS footprint, and
-// it outlives the pixel: in run mode every pixel of a sliding-window chain
-// but the first starts from the previous pixel's n*S (a one-pixel move) and
+// The covariance tiles (16 x 16, the upper block-triangle, some as their
+// transposes) are dealt so that wave w owns row block w.  Training vectors are
+// staged in LDS 16 at a time, split into BF16 parts (two for PREC 1, three for
+// PREC 0: as scm_split, so that the products run on the BF16 pipe beside the
+// other wave's VALU work), double-buffered: the global loads of the next chunk
+// are in flight while the waves run the MFMAs of the current one.  n S stays
+// in the accumulators, and S passes through LDS (its upper q x q blocks) to
+// the threads that solve.  In run mode every pixel of a sliding-window chain
+// but the first starts from the previous pixel's n S (a one-pixel move) and
 // stages only the training vectors that enter the stencil (added) and leave
 // it (subtracted), as the narrow FP32 kernels do.  LR-Kron runs on the
 // Hermitian half of S (Slots), one value of a slot per thread and held in its
@@ -2511,7 +2515,9 @@ __global__ __launch_bounds__(64, 2) void kstap_persistent(const KParams* __restr
 // barrier for A.  Sweeps over all blocks of S in LDS, with a pass of their own
 // for the block sums and four barriers, took the 512 x 512, p = 5, q = 24,
 // n = 256 frame 44.4 ms (FP32) and this 30.4 ms; p = 6, q = 16 in two passes
-// at 256 x 256 14.6 -> 9.9 ms.  The Hermitian time factors are queued
+// at 256 x 256 14.6 -> 9.9 ms.  With the split covariance in place of FP32
+// MFMA on staged FP32 (tiles dealt round-robin, S reloaded for every pixel)
+// 23.3 and 9.0 ms.  The time factors are queued as slots
 // in LDS and the batched tail (a6 + a8) runs 64/q' pixels per wave on waves
 // 0-3 at once.  Eight waves (two per SIMD, the LDS footprint allows one
 // workgroup per compute unit) hide each other's LDS, reduction and barrier
@@ -2531,15 +2537,17 @@ struct WideLds {
   static constexpr int G = Groups<Q>::G;
   static constexpr int NQ = kTailWaves * G;                          // pixels per batched tail
   static constexpr size_t kS = sizeof(float2) * NBLK * Q * (Q + 1);  // upper blocks of S
-  static constexpr size_t rowb = PREC ? 80 : 144;                    // padded bytes per staged row
-  static constexpr size_t stage1 = PREC ? 2 * NB * 16 * rowb : NB * 16 * rowb;   // hi + lo, or fp32
+  static constexpr int NPART = PREC ? 2 : 3;                         // BF16 parts of a staged sample
+  static constexpr size_t rowb = 80;                                 // padded bytes per staged row (16 vectors)
+  static constexpr size_t stage1 = NPART * NB * 16 * rowb;
   static constexpr size_t kStage = 2 * stage1;
-  static constexpr size_t kTail = sizeof(EC) * RBM * Q * G * kTailWaves;   // subspace scratch of the tail waves
+  static constexpr size_t kTail1 = tail_scratch_bytes<RBM, Q, G, EC>;      // subspace scratch of a tail wave
+  static constexpr size_t kTail = kTail1 * kTailWaves;
   static constexpr size_t kST = kStage > kTail ? kStage : kTail;
   static constexpr size_t oS = 0;
   static constexpr size_t oStage = (kS + 15) / 16 * 16;              // staging; tail scratch between pixels
-  static constexpr size_t oHq = oStage + (kST + 15) / 16 * 16;       // float2[NQ][Q*Q]: queued Herm(B)
-  static constexpr size_t oQUA = oHq + sizeof(float2) * NQ * Q * Q;  // EC[NQ][P*RAM]: queued U_A
+  static constexpr size_t oHq = oStage + (kST + 15) / 16 * 16;       // float2[NQ][Q*Q/2]: queued B, as slots
+  static constexpr size_t oQUA = oHq + sizeof(float2) * NQ * Q * Q / 2;   // EC[NQ][P*RAM]: queued U_A
   static constexpr size_t oUA = oQUA + sizeof(EC) * NQ * P * RAM;    // EC[P*RAM]
   static constexpr size_t oAh = oUA + sizeof(EC) * P * RAM;          // EC[P*P]
   static constexpr size_t oRedD = oAh + sizeof(EC) * P * P;          // double[kWideWaves]
@@ -2569,8 +2577,7 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
   constexpr int QQ = Q * Q;
   constexpr int NDT = (QQ + kWideThreads - 1) / kWideThreads;   // dimensions of b per thread
   constexpr int RAM = L::RAM;
-  constexpr int NPAIR = NB * (NB + 1) / 2;
-  constexpr int MYP = (NPAIR + kWideWaves - 1) / kWideWaves;   // tile pairs per wave (round-robin)
+  constexpr int MYP = NB / 2 + 1;   // tiles per wave at most
   constexpr int QP = Groups<Q>::QP;
   constexpr int G = L::G;
   constexpr int NQ = L::NQ;
@@ -2612,46 +2619,45 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
   }
   block_sync();
 
-  // this wave's tile pairs (I, J), I <= J, round-robin over the upper tiles
-  int pI[MYP], pJ[MYP];
-  bool pOk[MYP];
-  {
-    int t = 0;
+  // This wave's tiles: row block `wave` against column blocks wave + u mod NB,
+  // u < NB / 2, and u = NB / 2 for the first half of the waves (each tile of
+  // the upper block-triangle once, some as its transpose), so that a wave
+  // prepares one block's row operands for all its tiles.
+  static_assert(NB % 2 == 0 && NB <= kWideWaves, "one row block per wave");
+  const int nmine = wave >= NB ? 0 : NB / 2 + (wave < NB / 2 ? 1 : 0);
+  auto colblk = [&](int u) __attribute__((always_inline)) { return wave + u >= NB ? wave + u - NB : wave + u; };
+  f4 accR[MYP], accI[MYP];   // n S of the pixel processed last
 #pragma unroll
-    for (int I = 0; I < NB; ++I)
-#pragma unroll
-      for (int J = I; J < NB; ++J, ++t) {
-        if (t % kWideWaves == wave) {
-          pI[t / kWideWaves] = I;
-          pJ[t / kWideWaves] = J;
-        }
-      }
-#pragma unroll
-    for (int u = 0; u < MYP; ++u) pOk[u] = (u * kWideWaves + wave) < NPAIR;
-  }
+  for (int u = 0; u < MYP; ++u) accR[u] = accI[u] = f4{0.f, 0.f, 0.f, 0.f};
 
   constexpr int NIT = (16 * PQ + kWideThreads - 1) / kWideThreads;
   const int64_t plane = int64_t(H) * W * Q;
 
   // ------------------------------------------ a6 + a8 for the queued pixels
   // wave w < kTailWaves serves queue slots w*G .. w*G + G - 1; lane k of a
-  // slot's group takes row k of its Hermitian time factor (column k,
-  // conjugated: the stored factor is exactly Hermitian)
+  // slot's group takes row k of its Hermitian time factor
   auto tail = [&](int nfill) __attribute__((always_inline)) {
     int lanev = threadIdx.x & 63;
     asm volatile("" : "+v"(lanev));   // per call: no lane arithmetic hoisted out of the pixel loop
     const int lane = lanev;
     if (wave < kTailWaves) {   // uniform per wave; the tail syncs inside a wave only
       const int slot = wave * G + lane / QP, tk = lane % QP;
-      const bool own = slot < nfill && tk < Q;
       float2 Bq[Q];
-#pragma unroll
-      for (int l = 0; l < Q; ++l) Bq[l] = own ? cconj(sHq[(slot < nfill ? slot : 0) * QQ + l * Q + tk]) : cz();
-      EC* const scr = reinterpret_cast<EC*>(stage) + wave * (RBM * Q * G);
+      queue_row<P, Q>(sHq + slot * (QQ / 2), tk < Q ? tk : 0, Bq);   // empty slots: whatever is there, unused
+      char* const scr = stage + wave * L::kTail1;
       EC vb[RBM];
+#pragma unroll
+      for (int c = 0; c < RBM; ++c) vb[c] = czero<EC>();
       bool vb_ok;
-      tail_batch<P, Q, RBM, MODE, EC, true, VAR>(prm, Bq, slot, nfill, sQflag, sQidx, sQeta, sQit, sQUA, scr,
-                                                 PREC ? 1e-10 : 2e-6, vb, false, vb_ok);
+      if constexpr (VAR) {
+        tail_batch<P, Q, RBM, MODE, EC, true, true>(prm, Bq, slot, nfill, sQflag, sQidx, sQeta, sQit, sQUA,
+                                                    reinterpret_cast<EC*>(scr), PREC ? 1e-10 : 2e-6, vb, false, vb_ok);
+      } else {
+        with_rank<RBM>(r_b, [&](auto rank) __attribute__((always_inline)) {
+          tail_rows<P, Q, RBM, decltype(rank)::value, MODE, EC, true>(prm, Bq, wave * G, nfill, sQflag, sQidx, sQeta, sQit,
+                                                                      sQUA, scr, PREC ? 1e-10 : 2e-6, vb, false, vb_ok);
+        });
+      }
     }
     block_sync();
   };
@@ -2720,28 +2726,9 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
     const int cnt = slide ? prm.nadd[mv] + prm.nrem[mv] : n;
     const int npos = slide ? prm.nadd[mv] : n;
     const float fn = float(n);
-    // this lane's row and column inside a 16 x 16 tile.  On the mixed path
-    // they are made opaque, so that the S element addresses below are computed
-    // here, per pixel, instead of being hoisted out of the pixel loop (72 more
-    // live registers there, which spilled); the FP32 path has room for them.
-    int trow = 4 * (lane >> 4), tcol = lane & 15;
-    if constexpr (PREC == 1) asm volatile("" : "+v"(trow), "+v"(tcol));
-    f4 accR[MYP], accI[MYP];
+    if (!slide) {
 #pragma unroll
-    for (int u = 0; u < MYP; ++u) {
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        // element (a, b) of the old S, read from its upper block (conjugated
-        // when it lies below the block diagonal), without branches
-        const int a = 16 * pI[u] + trow + q4, b = 16 * pJ[u] + tcol;
-        const int ba = a / Q, bb = b / Q, ka = a - ba * Q, kb = b - bb * Q;
-        const bool upper = ba <= bb;
-        const int off = upper ? sblk<P, Q>(ba, bb) + ka * QS + kb : sblk<P, Q>(bb, ba) + kb * QS + ka;
-        const bool use = slide && pOk[u] && a < PQ && b < PQ;
-        const float2 v = sS[use ? off : 0];
-        accR[u][q4] = use ? v.x * fn : 0.f;
-        accI[u][q4] = use ? (upper ? v.y : -v.y) * fn : 0.f;
-      }
+      for (int u = 0; u < MYP; ++u) accR[u] = accI[u] = f4{0.f, 0.f, 0.f, 0.f};
     }
     const int nch = (cnt + 15) >> 4;
     float2 pre[NIT];
@@ -2762,20 +2749,12 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
       for (int it = 0; it < NIT; ++it) {
         int v, rho;
         if (!item(it, &v, &rho)) continue;
-        if constexpr (PREC == 1) {
-          const float a = pre[it].x, b = pre[it].y;
-          const __bf16 ha = (__bf16)a, hb = (__bf16)b;
-          const __bf16 la = (__bf16)(a - (float)ha), lb = (__bf16)(b - (float)hb);
-          __bf16* hrow = reinterpret_cast<__bf16*>(base + size_t(rho) * L::rowb);
-          __bf16* lrow = reinterpret_cast<__bf16*>(base + size_t(NB * 16 + rho) * L::rowb);
-          hrow[2 * v] = ha;
-          hrow[2 * v + 1] = hb;
-          lrow[2 * v] = la;
-          lrow[2 * v + 1] = lb;
-        } else {
-          float2* row = reinterpret_cast<float2*>(base + size_t(rho) * L::rowb);
-          row[v] = pre[it];
-        }
+        // part e of the pair (re, im), as split3 (the first two for PREC 1)
+        uint32_t part[3];
+        split3(pre[it].x, pre[it].y, part);
+#pragma unroll
+        for (int e = 0; e < L::NPART; ++e)
+          *reinterpret_cast<uint32_t*>(base + size_t(e * NB * 16 + rho) * L::rowb + 4 * v) = part[e];
       }
     };
     gload(0);
@@ -2786,50 +2765,38 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
       if (ch + 1 < nch) gload(ch + 1);
       const char* base = stage + buf * L::stage1;
       const int g = lane >> 4, rr = lane & 15;
-      if constexpr (PREC == 1) {
-        // operand of block I: row 16 I + rr, vectors 4g..4g+3 (re, im) = 16 bytes;
-        // the row operand of a subtracted vector is negated (sign bits of its pair)
+      if (wave < NB) {   // uniform
+        // operand of block I: row 16 I + rr, vectors 4g .. 4g + 3 (re, im) = 16
+        // bytes (rows past p q hold anything: they meet no stored element);
+        // the row operand of a subtracted vector is negated
+        auto ld = [&](int I, int e) __attribute__((always_inline)) -> u4 {
+          return *reinterpret_cast<const u4*>(base + size_t((e * NB + I) * 16 + rr) * L::rowb + g * 16);
+        };
         u4 msk;
 #pragma unroll
         for (int e = 0; e < 4; ++e) msk[e] = (ch * 16 + 4 * g + e >= npos) ? 0x80008000u : 0u;
-        auto ld = [&](int I, bool lo) __attribute__((always_inline)) -> u4 {
-          const int row = 16 * I + rr;
-          if (row >= PQ) return u4{0u, 0u, 0u, 0u};
-          const char* p = base + size_t((lo ? NB * 16 : 0) + row) * L::rowb + g * 16;
-          return *reinterpret_cast<const u4*>(p);
-        };
+        bf8 y[L::NPART], z[L::NPART];   // rows of Re and of Im
+#pragma unroll
+        for (int e = 0; e < L::NPART; ++e) {
+          y[e] = __builtin_bit_cast(bf8, ld(wave, e) ^ msk);
+          z[e] = swap_neg(y[e]);
+        }
+        // products of the parts: those below 2^-26 (three parts) or 2^-16 (two)
+        // of the leading one are dropped
+        constexpr int NPROD = L::NPART == 3 ? 6 : 3;
+        constexpr int pa3[6] = {2, 0, 1, 1, 0, 0}, pb3[6] = {0, 2, 1, 0, 1, 0}, pa2[3] = {0, 0, 1}, pb2[3] = {0, 1, 0};
 #pragma unroll
         for (int u = 0; u < MYP; ++u) {
-          if (!pOk[u]) continue;
-          const bf8 hI = __builtin_bit_cast(bf8, ld(pI[u], false) ^ msk);
-          const bf8 lI = __builtin_bit_cast(bf8, ld(pI[u], true) ^ msk);
-          const bf8 hJ = __builtin_bit_cast(bf8, ld(pJ[u], false)), lJ = __builtin_bit_cast(bf8, ld(pJ[u], true));
-          const bf8 zh = swap_neg(hI), zl = swap_neg(lI);
-          accR[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hI, hJ, accR[u], 0, 0, 0);
-          accI[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zh, hJ, accI[u], 0, 0, 0);
-          accR[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hI, lJ, accR[u], 0, 0, 0);
-          accI[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zh, lJ, accI[u], 0, 0, 0);
-          accR[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lI, hJ, accR[u], 0, 0, 0);
-          accI[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zl, hJ, accI[u], 0, 0, 0);
-        }
-      } else {
-        // 4 K-steps of 4 vectors: lane (row rr, vector 4 s + g)
+          if (u >= nmine) continue;   // uniform
+          const int J = colblk(u);
+          bf8 c[L::NPART];
 #pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) {
-          const float sg = (ch * 16 + 4 * s4 + g >= npos) ? -1.f : 1.f;
-          auto ld = [&](int I) __attribute__((always_inline)) -> float2 {
-            const int row = 16 * I + rr;
-            if (row >= PQ) return cz();
-            return reinterpret_cast<const float2*>(base + size_t(row) * L::rowb)[4 * s4 + g];
-          };
+          for (int e = 0; e < L::NPART; ++e) c[e] = __builtin_bit_cast(bf8, ld(J, e));
 #pragma unroll
-          for (int u = 0; u < MYP; ++u) {
-            if (!pOk[u]) continue;
-            const float2 a = cscale(ld(pI[u]), sg), b = ld(pJ[u]);
-            accR[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, accR[u], 0, 0, 0);
-            accI[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.x, accI[u], 0, 0, 0);
-            accR[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, accR[u], 0, 0, 0);
-            accI[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(-a.x, b.y, accI[u], 0, 0, 0);
+          for (int w = 0; w < NPROD; ++w) {
+            const int ea = L::NPART == 3 ? pa3[w] : pa2[w], eb = L::NPART == 3 ? pb3[w] : pb2[w];
+            accR[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(y[ea], c[eb], accR[u], 0, 0, 0);
+            accI[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z[ea], c[eb], accI[u], 0, 0, 0);
           }
         }
       }
@@ -2837,18 +2804,21 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
       block_sync();
     }
     // S to LDS as upper blocks: every element (a, b), a <= b, has one writer
-    // (the staging barrier above also ends every wave's reload of the old S)
-    block_sync();
+    // (the staging barrier above also ends every wave's use of the old S)
     {
-      if constexpr (PREC == 1) asm volatile("" : "+v"(trow), "+v"(tcol));   // as above
+      int trow = 4 * (lane >> 4), tcol = lane & 15;
       const float inv_n = 1.f / fn;
 #pragma unroll
       for (int u = 0; u < MYP; ++u) {
-        if (!pOk[u]) continue;
+        if (u >= nmine) continue;   // uniform
+        const int J = colblk(u);
+        const bool up = J >= wave;   // uniform: the tile, or its transpose, lies above the diagonal
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
-          const int a = 16 * pI[u] + trow + q4, b = 16 * pJ[u] + tcol;
-          if (a < PQ && b < PQ && a <= b) sput<P, Q>(sS, a, b, make_float2(accR[u][q4] * inv_n, accI[u][q4] * inv_n));
+          const int r1 = 16 * wave + trow + q4, c1 = 16 * J + tcol;
+          const int a = up ? r1 : c1, b = up ? c1 : r1;
+          if (a < PQ && b < PQ && a <= b)
+            sput<P, Q>(sS, a, b, make_float2(accR[u][q4] * inv_n, (up ? accI[u][q4] : -accI[u][q4]) * inv_n));
         }
       }
     }
@@ -3145,17 +3115,10 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
     ua_ok = !zero && !bad;
     block_sync();
     // ------------------------------------------ enqueue for the batched tail
-    // the Hermitian B from its slots
-    {
-      float* const f = reinterpret_cast<float*>(sHq + nq * QQ);
 #pragma unroll
-      for (int t = 0; t < NDT; ++t) {
-        if (!has[t]) continue;
-        const int dk = comp[t] ? lb[t] : kb[t];
-        f[dgl[t] ? 2 * (dk * Q + dk) : 2 * (kb[t] * Q + lb[t]) + comp[t]] = bv[t];
-        f[dgl[t] ? 2 * (dk * Q + dk) + 1 : 2 * (lb[t] * Q + kb[t]) + comp[t]] =
-            dgl[t] ? 0.f : (comp[t] ? -bv[t] : bv[t]);
-      }
+    for (int t = 0; t < NDT; ++t) {
+      const int e = tid + kWideThreads * t;
+      if (e < QQ) reinterpret_cast<float*>(sHq)[nq * QQ + 2 * (e - comp[t] * (QQ / 2)) + comp[t]] = bv[t];
     }
     if (tid == 0) {
       sQidx[nq] = idx;

@@ -101,6 +101,8 @@ const void* persistent_kernel(int cls) {
   return table()[cls]->persist_fn;
 }
 
+int persistent_wgs(int cls) { return cls < 0 || cls >= int(table().size()) ? 8 : table()[cls]->wgs; }
+
 int launch_split(const float2* x, uint32_t* xs, int64_t n, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(split_planes, dim3(split_grid(n)), dim3(256), 0, stream, x, xs, n);

@@ -207,6 +207,7 @@ struct Entry {
   int (*persist)(const KParams* descs, const int32_t* order, const int64_t* prefix, int nt, int ppb,
                  unsigned long long* counter, int grid, hipStream_t stream);   // null: no persistent form
   const void* persist_fn;
+  int wgs;       // persistent workgroups that one compute unit holds
 };
 
 // Returns true if a kernel is built for (p, q, r_b bound, precision).
@@ -250,6 +251,10 @@ inline unsigned split_grid(int64_t n) {
 
 // Zeroes n device counters with a kernel (no memset node in graphs).
 int launch_reset(unsigned long long* counters, int n, hipStream_t stream);
+
+// Workgroups of class `cls` that one compute unit holds: the persistent grid is
+// this times the compute units (times a tuned multiple).
+int persistent_wgs(int cls);
 
 // Host handles of the persistent kernel of class `cls` (arguments: descs,
 // order, prefix, nt, ppb, counter) and of the counter-reset kernel

@@ -197,7 +197,7 @@ class HipExec : public ks::Exec {
       const auto& L = launches[c];
       const int nt = int(by_cls[L.first].size());
       le = kstap::launch_persistent(L.first, s.d_desc, s.d_order + L.second.first, s.d_prefix + L.second.second, nt,
-                                    ppb, s.d_ctr + c * kstap::kQueues, cus * 8, s_comp);
+                                    ppb, s.d_ctr + c * kstap::kQueues, cus * kstap::persistent_wgs(L.first), s_comp);
     }
     if (le == hipSuccess) le = hipEventRecord(s.ev, s_comp);
     return check(hipError_t(le));

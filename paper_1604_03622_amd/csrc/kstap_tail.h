@@ -1,7 +1,7 @@
-// a6 + a8 of the narrow kernels' plain statistic, batched: top-r_b time
+// a6 + a8 of the plain statistic, batched: top-r_b time
 // subspace, projected test vector and statistic of up to 64 / QP queued pixels
-// of one wavefront (the statistic variants and the wide kernels take
-// tail_batch, which has the Doppler bank, the filters and the passes).
+// of one wavefront (the statistic variants take tail_batch, which has the
+// Doppler bank, the filters and the passes).
 //
 // Bound by VALU issue, a third of it lane-group reductions.  Against
 // tail_batch, whose loops run to a run-time rank and mask absent rows at every
@@ -71,7 +71,7 @@ constexpr size_t tail_scratch_bytes = size_t(G) * (sizeof(C) * R * D + 16);
 // subspace of one Hermitian D x D matrix per lane group.  v enters as the
 // start block (not tested: a kept neighbour's basis or a fixed generic one)
 // and leaves as the basis.  Same iteration, stopping rule and freezing.
-template <int R, int QP, int D, typename C>
+template <int R, int QP, int D, typename C, bool WAVE_LOCAL>
 __device__ __forceinline__ void rows_subspace(const float2 (&mrow)[D], int g, int k, C (&v)[R], char* scratch,
                                               int max_steps, double tol) {
   using S = decltype(C{}.x);
@@ -82,7 +82,7 @@ __device__ __forceinline__ void rows_subspace(const float2 (&mrow)[D], int g, in
 #pragma unroll
       for (int c = 0; c < R; ++c) sV[k * R + c] = v[c];
     }
-    wave_sync();
+    lds_sync<WAVE_LOCAL>();
     C w[R];
 #pragma unroll
     for (int c = 0; c < R; ++c) w[c] = czero<C>();
@@ -119,7 +119,7 @@ __device__ __forceinline__ void rows_subspace(const float2 (&mrow)[D], int g, in
     // column's past the test below, and holds (spills) all rows until then
 #pragma unroll
     for (int c = 0; c < R; ++c) asm volatile("" : "+v"(w[c].x), "+v"(w[c].y));
-    wave_sync();
+    lds_sync<WAVE_LOCAL>();
     bool conv = false;
     if (tested) {
       // residual W - V (V^H W), V^H W Hermitian: one row of it at a time
@@ -166,13 +166,13 @@ __device__ __forceinline__ void rows_subspace(const float2 (&mrow)[D], int g, in
   }
 }
 
-// The batched tail for r_b = R.  Arguments as tail_batch: lane group g serves
-// queue slot g, whose lane k holds row k of the pixel's Hermitian
+// The batched tail for r_b = R.  Arguments as tail_batch: lane group g of this
+// wavefront serves queue slot slot0 + g, whose lane k holds row k of the pixel's Hermitian
 // time factor in Bq (cleared here in empty and flagged slots); vb: this lane's
 // row of its slot's basis, on entry the start of the slots whose lanes set
 // `keep`, on return the basis.
-template <int P, int Q, int RBM, int R, int MODE, typename EC>
-__device__ __forceinline__ void tail_rows(const KParams& prm, float2 (&Bq)[Q], int nfill, const int* sQflag,
+template <int P, int Q, int RBM, int R, int MODE, typename EC, bool WAVE_LOCAL>
+__device__ __forceinline__ void tail_rows(const KParams& prm, float2 (&Bq)[Q], int slot0, int nfill, const int* sQflag,
                                           const int64_t* sQidx, const float* sQeta, const int* sQit,
                                           const EC (*sQUA)[P * ((P < kMaxRA) ? P : kMaxRA)], char* scratch, double tol,
                                           EC (&vb)[RBM], bool keep, bool& vb_ok) {
@@ -184,9 +184,9 @@ __device__ __forceinline__ void tail_rows(const KParams& prm, float2 (&Bq)[Q], i
   // steering entries are formed here, once per batch, instead of being hoisted
   // out of the pixel loop, where they would be spilled (187 x 233, q = 12,
   // r_b = 6 takes 966 us with them hoisted)
-  int lane = threadIdx.x;
+  int lane = threadIdx.x & 63;
   asm volatile("" : "+v"(lane));
-  const int tk = lane % QP, slot = lane / QP;
+  const int tk = lane % QP, slot = slot0 + lane / QP;
   const int H = prm.H, W = prm.W;
   const int r_a = prm.r_a;
   const bool slot_ok = slot < nfill;
@@ -211,7 +211,7 @@ __device__ __forceinline__ void tail_rows(const KParams& prm, float2 (&Bq)[Q], i
     // FP64 solves iterate until converged where the r_b-th and next eigenvalues
     // of B lie close together (a ratio of 0.99 takes ~1 500 steps to 1e-10);
     // the loop exits on the step cap, so a group never runs unbounded
-    rows_subspace<R, QP, Q, EC>(Bq, slot, tk, v, scratch, sizeof(ES) == 8 ? 4000 : 200, tol);
+    rows_subspace<R, QP, Q, EC, WAVE_LOCAL>(Bq, lane / QP, tk, v, scratch, sizeof(ES) == 8 ? 4000 : 200, tol);
 #pragma unroll
     for (int c = 0; c < R; ++c) vb[c] = v[c];
   }
@@ -306,7 +306,24 @@ __device__ __forceinline__ void tail_rows(const KParams& prm, float2 (&Bq)[Q], i
       for (int c = 0; c < R; ++c) prm.UB[(pidx * Q + tk) * R + c] = (flag != 0) ? cz() : tof(v[c]);
     }
   }
-  wave_sync();
+  lds_sync<WAVE_LOCAL>();
+}
+
+// f(Int<r_b>()): r_b as a constant (r_b > 4 takes the RBM = 8 classes).
+template <int RBM, typename F>
+__device__ __forceinline__ void with_rank(int r_b, F f) {
+  if constexpr (RBM == 4) {
+    if (r_b == 4) f(Int<4>());
+    else if (r_b == 3) f(Int<3>());
+    else if (r_b == 2) f(Int<2>());
+    else if (r_b == 1) f(Int<1>());
+    else f(Int<0>());
+  } else {
+    if (r_b == 8) f(Int<8>());
+    else if (r_b == 7) f(Int<7>());
+    else if (r_b == 6) f(Int<6>());
+    else f(Int<5>());
+  }
 }
 
 }  // namespace
