@@ -2986,12 +2986,19 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
           }
           return;
         }
-        // r_a > 1: subspace iteration with lane k holding row k of A' and of
-        // the basis (dot products by wave reductions), warm-started from the
-        // previous U_A; then Hs = U^H A' U (r_a x r_a) and A = U Hs U^H, entry
-        // (i, j) on lane i P + j
-        EC* const sVs = reinterpret_cast<EC*>(stage);   // [RAM][P] basis exchange (the staging area is free)
-        EC* const sHs = sVs + RAM * P;                  // [RAM][RAM]
+        // r_a > 1: subspace iteration with lane k < P holding row k of A' and
+        // of the basis, warm-started from the previous U_A; then Hs = U^H A' U
+        // (r_a x r_a) and A = U Hs U^H, entry (i, j) on lane i P + j.  The
+        // staging area is free and holds the basis exchange and Hs.  FP32: a
+        // group of 8 lanes (the others rows of zeros) and r_a a constant, two
+        // passes of p = 6, q = 16 at 128 x 128 2.27 -> 1.68 ms against the
+        // whole wave and a run-time rank, which the FP64 solves keep (their
+        // unrolled bases spill: p = 5, q = 24 at 192 x 192 6.5 -> 7.3 ms).
+        static_assert(P <= 8, "a row per lane of a group of 8");
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));   // nothing of this path is hoisted out of the iteration
+        EC* const sHs = reinterpret_cast<EC*>(stage);                               // [RAM][RAM]
+        char* const scr = stage + (sizeof(EC) * RAM * RAM + 15) / 16 * 16;           // basis exchange
         if (lane < P * P) sAr[lane] = mine * binv;
         lane_sync();
         const int ai = lane / P, aj = lane - (lane / P) * P;
@@ -3006,37 +3013,75 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
         const bool rowk = lane < P;
         float2 mrow[P];
 #pragma unroll
-        for (int j = 0; j < P; ++j) mrow[j] = tof(sAh[(rowk ? lane : 0) * P + j]);
-        EC va[RAM];
+        for (int j = 0; j < P; ++j) mrow[j] = rowk ? tof(sAh[lane * P + j]) : cz();
+        if constexpr (PREC == 0) {
+          auto solve = [&](auto rank) __attribute__((always_inline)) {
+            constexpr int R = decltype(rank)::value;
+            EC va[R];
 #pragma unroll
-        for (int c = 0; c < RAM; ++c) va[c] = (!cold && rowk) ? sUA[lane * RAM + c] : czero<EC>();
-        group_subspace<RAM, 64, P, EC, true>(mrow, rowk, r_a, va, sVs, cold, 500, PREC ? 1e-12 : 2e-6);
-        lane_sync();
-        if (rowk) {
+            for (int c = 0; c < R; ++c)
+              va[c] = !rowk ? czero<EC>() : cold ? cto<EC>(omega(lane, c)) : sUA[lane * RAM + c];
+            rows_subspace<R, 8, P, EC, true>(mrow, lane >> 3, lane & 7, va, scr, 500, 2e-6, !cold);
+            if (rowk) {
 #pragma unroll
-          for (int c = 0; c < RAM; ++c)
-            if (c < r_a) sUA[lane * RAM + c] = va[c];
-        }
-        lane_sync();
-        // (A' U)[k][b] on lane k, then Hs[a][b] = sum_k conj(U[k][a]) (A' U)[k][b]
-        EC au[RAM];
-#pragma unroll
-        for (int b = 0; b < RAM; ++b) {
-          au[b] = czero<EC>();
-          if (b < r_a && rowk) {
-#pragma unroll
-            for (int j = 0; j < P; ++j) au[b] = cfma(sAh[lane * P + j], sUA[j * RAM + b], au[b]);
-          }
-        }
-#pragma unroll
-        for (int a2 = 0; a2 < RAM; ++a2)
-#pragma unroll
-          for (int b = 0; b < RAM; ++b)
-            if (a2 < r_a && b < r_a) {
-              const EC hs = gsum<64>(rowk ? ccfma(va[a2], au[b], czero<EC>()) : czero<EC>());
-              if (lane == 0) sHs[a2 * RAM + b] = hs;
+              for (int c = 0; c < R; ++c) sUA[lane * RAM + c] = va[c];
             }
-        lane_sync();
+            lane_sync();
+            // (A' U)[k][b] on lane k, then Hs[a][b] = sum_k conj(U[k][a]) (A' U)[k][b]
+            EC au[R], hs[R][R];
+#pragma unroll
+            for (int b = 0; b < R; ++b) {
+              au[b] = czero<EC>();
+#pragma unroll
+              for (int j = 0; j < P; ++j) au[b] = cfma(cto<EC>(mrow[j]), sUA[j * RAM + b], au[b]);
+            }
+#pragma unroll
+            for (int a2 = 0; a2 < R; ++a2)
+#pragma unroll
+              for (int b = 0; b < R; ++b) hs[a2][b] = gsum<8>(ccmul(va[a2], au[b]));
+            if (lane == 0) {
+#pragma unroll
+              for (int a2 = 0; a2 < R; ++a2)
+#pragma unroll
+                for (int b = 0; b < R; ++b) sHs[a2 * RAM + b] = hs[a2][b];
+            }
+          };
+          if (r_a == 2) solve(Int<2>());
+          else if (r_a == 3) solve(Int<3>());
+          else solve(Int<RAM>());
+          lane_sync();
+        } else {
+          EC va[RAM];
+#pragma unroll
+          for (int c = 0; c < RAM; ++c) va[c] = (!cold && rowk) ? sUA[lane * RAM + c] : czero<EC>();
+          group_subspace<RAM, 64, P, EC, true>(mrow, rowk, r_a, va, reinterpret_cast<EC*>(scr), cold, 500, 1e-12);
+          lane_sync();
+          if (rowk) {
+#pragma unroll
+            for (int c = 0; c < RAM; ++c)
+              if (c < r_a) sUA[lane * RAM + c] = va[c];
+          }
+          lane_sync();
+          // (A' U)[k][b] on lane k, then Hs[a][b] = sum_k conj(U[k][a]) (A' U)[k][b]
+          EC au[RAM];
+#pragma unroll
+          for (int b = 0; b < RAM; ++b) {
+            au[b] = czero<EC>();
+            if (b < r_a && rowk) {
+#pragma unroll
+              for (int j = 0; j < P; ++j) au[b] = cfma(sAh[lane * P + j], sUA[j * RAM + b], au[b]);
+            }
+          }
+#pragma unroll
+          for (int a2 = 0; a2 < RAM; ++a2)
+#pragma unroll
+            for (int b = 0; b < RAM; ++b)
+              if (a2 < r_a && b < r_a) {
+                const EC hs = gsum<64>(rowk ? ccfma(va[a2], au[b], czero<EC>()) : czero<EC>());
+                if (lane == 0) sHs[a2 * RAM + b] = hs;
+              }
+          lane_sync();
+        }
         if (lane < P * P && ai <= aj) {
           EC acc2 = czero<EC>();
           for (int a2 = 0; a2 < r_a; ++a2) {

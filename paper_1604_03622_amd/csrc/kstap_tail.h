@@ -69,14 +69,14 @@ constexpr size_t tail_scratch_bytes = size_t(G) * (sizeof(C) * R * D + 16);
 
 // group_subspace for exactly R columns and zero rows: the top-R invariant
 // subspace of one Hermitian D x D matrix per lane group.  v enters as the
-// start block (not tested: a kept neighbour's basis or a fixed generic one)
-// and leaves as the basis.  Same iteration, stopping rule and freezing.
+// start block (tested at the first step if `tested`) and leaves as the basis.
+// Same iteration, stopping rule and freezing.
 template <int R, int QP, int D, typename C, bool WAVE_LOCAL>
 __device__ __forceinline__ void rows_subspace(const float2 (&mrow)[D], int g, int k, C (&v)[R], char* scratch,
-                                              int max_steps, double tol) {
+                                              int max_steps, double tol, bool tested = false) {
   using S = decltype(C{}.x);
   C* const sV = reinterpret_cast<C*>(scratch + g * (sizeof(C) * R * D + 16));
-  bool tested = false, done = false;
+  bool done = false;
   for (int step = 0; step < max_steps; ++step) {
     if (k < D) {
 #pragma unroll
@@ -89,7 +89,7 @@ __device__ __forceinline__ void rows_subspace(const float2 (&mrow)[D], int g, in
     // rows of the basis come two at a time (one for wide or FP64 bases), the
     // next ones in flight while the current ones are used; without the
     // scheduling barriers all D rows are loaded at once and spill
-    constexpr int GR = sizeof(C) * R <= 32 ? 2 : 1, NG = D / GR;
+    constexpr int GR = (sizeof(C) * R <= 32 && D % 2 == 0) ? 2 : 1, NG = D / GR;
     static_assert(D % GR == 0, "rows in groups");
     C buf[2][GR][R];
     auto load = [&](int gi, C (&to)[GR][R]) __attribute__((always_inline)) {
