@@ -49,6 +49,97 @@ static_assert(sizeof(float2) * (kStageMax + kLrkMaxRows) <= kRegion, "staged chu
 // P: channels, a compile-time constant so that the p x p matrices of the
 // iteration live in registers.
 //
+// Entry e of the upper triangle of an np x np matrix, row-major: (u, v), u <= v.
+__device__ __forceinline__ void tri_entry(int e, int np, int* u, int* v) {
+  int r = 0;
+  while (e >= np - r) {
+    e -= np - r;
+    ++r;
+  }
+  *u = r;
+  *v = r + e;
+}
+
+// The Gram sums of lrk_solve over many workgroups: one workgroup's FP64 sums of
+// FP32 products over its `span` samples (64 at a time through LDS), real parts
+// then imaginary parts of the nent entries, to part[block].  One workgroup
+// reads the snapshots at 34 ns a sample, 85 of the 125 us at p = 3, n = 5,
+// q = 2 500 with the rest of the card idle; spread out, the sums take a few.
+// The partial sums lie in B-hat's own memory, which lrk_emit_b then overwrites.
+constexpr int kGramChunk = 64;
+constexpr int kGramMaxBlocks = 64;
+constexpr int kGramMinQ = 256;
+constexpr int kGramMinWork = 32768;   // entries x samples
+__global__ __launch_bounds__(kSolveThreads) void lrk_gram(const float2* __restrict__ X, int np, int q, int span,
+                                                          double* __restrict__ part) {
+  __shared__ float2 sX[kLrkMaxRows * (kGramChunk + 1)];
+  __shared__ double sP[2 * kSolveThreads];
+  const int tid = threadIdx.x;
+  const int ntri = np * (np + 1) / 2, nent = ntri + np;
+  const bool grouped = nent <= kSolveThreads;
+  const int G = grouped ? kSolveThreads / nent : 1, grp = grouped ? tid / nent : 0;
+  const int k0 = blockIdx.x * span, k1 = min(q, k0 + span);
+  int eu[kMaxEnt], ev[kMaxEnt], ne = 0;
+  double ar[kMaxEnt], ai[kMaxEnt];
+#pragma unroll
+  for (int j = 0; j < kMaxEnt; ++j) {
+    const int e = grouped ? (j == 0 && grp < G ? tid - grp * nent : nent) : tid + j * kSolveThreads;
+    eu[j] = 0;
+    ev[j] = -1;   // a row sum
+    ar[j] = ai[j] = 0.0;
+    if (e < nent) {
+      ne = j + 1;
+      if (e >= ntri) eu[j] = e - ntri;
+      else tri_entry(e, np, &eu[j], &ev[j]);
+    }
+  }
+  for (int kc = k0; kc < k1; kc += kGramChunk) {
+    const int len = min(kGramChunk, k1 - kc);
+    __syncthreads();   // the previous chunk is consumed
+    for (int e = tid; e < np * kGramChunk; e += kSolveThreads) {
+      const int u = e / kGramChunk, k = e - u * kGramChunk;
+      if (k < len) sX[u * (kGramChunk + 1) + k] = X[int64_t(u) * q + kc + k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kMaxEnt; ++j) {
+      if (j >= ne) continue;
+      const float2* const ra = sX + eu[j] * (kGramChunk + 1);
+      const bool rowsum = ev[j] < 0;
+      const float2* const rb = sX + (rowsum ? 0 : ev[j]) * (kGramChunk + 1);
+#pragma unroll 4
+      for (int k = grp; k < len; k += G) {
+        const float2 a = ra[k];
+        const float2 b = rowsum ? make_float2(1.f, 0.f) : rb[k];   // a * conj(b)
+        ar[j] += double(a.x) * double(b.x) + double(a.y) * double(b.y);
+        ai[j] += double(a.y) * double(b.x) - double(a.x) * double(b.y);
+      }
+    }
+  }
+  double* const out = part + int64_t(blockIdx.x) * 2 * nent;
+  if (grouped) {
+    sP[tid] = ar[0];
+    sP[kSolveThreads + tid] = ai[0];
+    __syncthreads();
+    if (tid < nent) {
+      double r = 0.0, i = 0.0;
+      for (int g2 = 0; g2 < G; ++g2) {
+        r += sP[g2 * nent + tid];
+        i += sP[kSolveThreads + g2 * nent + tid];
+      }
+      out[tid] = r;
+      out[nent + tid] = i;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < kMaxEnt; ++j)
+      if (j < ne) {
+        out[tid + j * kSolveThreads] = ar[j];
+        out[nent + tid + j * kSolveThreads] = ai[j];
+      }
+  }
+}
+
 // Gram phase: entry e of the upper triangle (or row sum) of the n p snapshot
 // rows belongs to one thread per sample group; every thread keeps its FP64
 // sums of FP32 products in registers over all chunks (the chunks, as long as
@@ -60,8 +151,12 @@ static_assert(sizeof(float2) * (kStageMax + kLrkMaxRows) <= kRegion, "staged chu
 // partial sums of M = sum T_(m,m') G_mm' and tb = Re sum tr(T_(m,m') T_(m',m))
 // over pair subsets; wave 0 adds them, takes EIG_{r_a} (parallel Jacobi, one
 // lane per matrix entry) and the stop decision.
+//
+// For many samples the Gram sums of nparts workgroups (lrk_gram) are read from
+// `part` instead.
 template <int P>
-__global__ __launch_bounds__(kSolveThreads) void lrk_solve(const float2* __restrict__ X, LrkParams prm) {
+__global__ __launch_bounds__(kSolveThreads) void lrk_solve(const float2* __restrict__ X, LrkParams prm,
+                                                           const double* __restrict__ part, int nparts) {
   constexpr int p = P;
   const int n = prm.n, q = prm.q, np = n * p;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -93,14 +188,8 @@ __global__ __launch_bounds__(kSolveThreads) void lrk_solve(const float2* __restr
       ne = j + 1;
       if (e >= ntri) {
         eu[j] = e - ntri;
-      } else {   // e -> (u, v), u <= v, row-major over the upper triangle
-        int u = 0, rem = e;
-        while (rem >= np - u) {
-          rem -= np - u;
-          ++u;
-        }
-        eu[j] = u;
-        ev[j] = u + rem;
+      } else {
+        tri_entry(e, np, &eu[j], &ev[j]);
       }
     }
   }
@@ -121,8 +210,21 @@ __global__ __launch_bounds__(kSolveThreads) void lrk_solve(const float2* __restr
       pre[j] = (u < np && k < len) ? X[int64_t(u) * q + k0 + k] : make_float2(0.f, 0.f);
     }
   };
-  const int nch = (q + chunk - 1) / chunk;
-  load_chunk(0);
+  const int nch = part ? 0 : (q + chunk - 1) / chunk;
+  if (part) {
+#pragma unroll
+    for (int j = 0; j < kMaxEnt; ++j) {
+      if (j >= ne) continue;
+      const int e = grouped ? tid - grp * nent : tid + j * kSolveThreads;
+#pragma unroll 4
+      for (int w = grp; w < nparts; w += G) {
+        ar[j] += part[(2 * w) * nent + e];
+        ai[j] += part[(2 * w + 1) * nent + e];
+      }
+    }
+  } else {
+    load_chunk(0);
+  }
   for (int ch = 0; ch < nch; ++ch) {
     const int len = min(chunk, q - ch * chunk);
     __syncthreads();   // the previous chunk is consumed
@@ -431,20 +533,34 @@ __global__ __launch_bounds__(256) void lrk_emit_b(const float2* __restrict__ X, 
 
 int launch_lrkron(const float2* X, const LrkParams& prm, hipStream_t stream) {
   if (prm.n * prm.p > kLrkMaxRows || prm.p > kLrkMaxP || prm.p < 1 || prm.q < 1) return hipErrorInvalidValue;
+  // Many workgroups for the Gram sums where one would take most of the time and
+  // B-hat's memory, written last, holds their partial sums.  One workgroup
+  // against many, p, q, n: 3, 256, 5 47.1 / 44.4 us; 3, 512, 5 48.7 / 38.8;
+  // 3, 2500, 5 121 / 51; 6, 256, 5 108 / 96; 6, 1250, 5 200 / 101; 1, 4000, 64
+  // 1 778 / 294; but 2, 260, 3 (7 020 entries x samples) 22.7 / 23.7: there the
+  // extra launch costs more than it saves.
+  const int np = prm.n * prm.p, nent = np * (np + 1) / 2 + np;
+  const int span = kGramChunk * ((prm.q + kGramChunk * kGramMaxBlocks - 1) / (kGramChunk * kGramMaxBlocks));
+  const int nparts = (prm.q + span - 1) / span;
+  double* part = nullptr;
+  if (prm.B && prm.q >= kGramMinQ && int64_t(nent) * prm.q >= kGramMinWork &&
+      size_t(nparts) * 2 * nent * sizeof(double) <= size_t(prm.q) * prm.q * sizeof(float2)) {
+    part = reinterpret_cast<double*>(prm.B);
+    hipLaunchKernelGGL(lrk_gram, dim3(nparts), dim3(kSolveThreads), 0, stream, X, np, prm.q, span, part);
+  }
   switch (prm.p) {
-    case 1: hipLaunchKernelGGL(lrk_solve<1>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm); break;
-    case 2: hipLaunchKernelGGL(lrk_solve<2>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm); break;
-    case 3: hipLaunchKernelGGL(lrk_solve<3>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm); break;
-    case 4: hipLaunchKernelGGL(lrk_solve<4>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm); break;
-    case 5: hipLaunchKernelGGL(lrk_solve<5>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm); break;
-    case 6: hipLaunchKernelGGL(lrk_solve<6>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm); break;
-    case 7: hipLaunchKernelGGL(lrk_solve<7>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm); break;
-    default: hipLaunchKernelGGL(lrk_solve<8>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm); break;
+    case 1: hipLaunchKernelGGL(lrk_solve<1>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
+    case 2: hipLaunchKernelGGL(lrk_solve<2>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
+    case 3: hipLaunchKernelGGL(lrk_solve<3>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
+    case 4: hipLaunchKernelGGL(lrk_solve<4>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
+    case 5: hipLaunchKernelGGL(lrk_solve<5>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
+    case 6: hipLaunchKernelGGL(lrk_solve<6>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
+    case 7: hipLaunchKernelGGL(lrk_solve<7>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
+    default: hipLaunchKernelGGL(lrk_solve<8>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !prm.B) return e;
   const unsigned t = unsigned((prm.q + kTile - 1) / kTile);
-  const int np = prm.n * prm.p;
   const size_t lds = sizeof(float2) * (size_t(kTile) * (np + 1) + size_t(np) * (kTile + 1));
   hipLaunchKernelGGL(lrk_emit_b, dim3(t, t), dim3(256), lds, stream, X, prm);
   return hipGetLastError();
