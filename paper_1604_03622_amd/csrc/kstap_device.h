@@ -1289,32 +1289,15 @@ __device__ __forceinline__ void split_store(const SplitAcc<P, Q>& acc, int n, fl
 // sample: hi first, then lo.  The covariance kernel loads MFMA operands
 // straight from them.  In a 16-vector chunk, 16-lane group g of the
 // wavefront holds vectors 4g .. 4g + 3.
-//   Re S tiles: v_mfma_f32_16x16x32_bf16 on Y = (re, im) pairs, which sums
-//     re_I re_J + im_I im_J over the 16 vectors of the chunk.
-//   Im S tiles: v_mfma_f32_16x16x16_bf16 on single components,
-//     im_I re_J^T + (-re_I) im_J^T; the operands are half-word gathers (and
-//     one sign flip) of the loaded pairs.
-__device__ __forceinline__ void split_bf16(const float2 (&v)[4], bf8& hi, bf8& lo) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float a = v[e].x, b = v[e].y;
-    const __bf16 ha = (__bf16)a, hb = (__bf16)b;
-    hi[2 * e] = ha;
-    hi[2 * e + 1] = hb;
-    lo[2 * e] = (__bf16)(a - (float)ha);
-    lo[2 * e + 1] = (__bf16)(b - (float)hb);
-  }
-}
+//   Both tiles of v_mfma_f32_16x16x32_bf16 over the 16 vectors of the chunk:
+//   Re S on Y = (re, im) pairs, re_I re_J + im_I im_J; Im S with the row
+//   operand (im, -re), im_I re_J - re_I im_J.
 __device__ __forceinline__ bf8 swap_neg(bf8 y) {
   u4 w = __builtin_bit_cast(u4, y);
 #pragma unroll
   for (int e = 0; e < 4; ++e) w[e] = ((w[e] >> 16) | (w[e] << 16)) ^ 0x80000000u;
   return __builtin_bit_cast(bf8, w);
 }
-
-// re (low halves) and im (high halves) of two packed pairs, as one dword
-__device__ __forceinline__ uint32_t lo_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
-__device__ __forceinline__ uint32_t hi_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
 template <int P, int Q>
 __device__ __forceinline__ void scm_bf16x3(const uint32_t* hwin, const uint32_t* lwin, int64_t plane, uint32_t rec,
@@ -1350,21 +1333,13 @@ __device__ __forceinline__ void scm_bf16x3(const uint32_t* hwin, const uint32_t*
   };
   // MFMAs of one 16-vector chunk
   auto accumulate = [&](const u4 (&v)[2][NB]) {
-    bf8 yh[NB], yl[NB];
-    s4 reh[NB], rel[NB], imh[NB], iml[NB], nreh[NB], nrel[NB];
+    bf8 yh[NB], yl[NB], zh[NB], zl[NB];   // (re, im) and (im, -re)
 #pragma unroll
     for (int I = 0; I < NB; ++I) {
-      const u4 h = v[0][I], l = v[1][I];
-      yh[I] = __builtin_bit_cast(bf8, h);
-      yl[I] = __builtin_bit_cast(bf8, l);
-      const u2 rh2{lo_halves(h[0], h[1]), lo_halves(h[2], h[3])};
-      const u2 rl2{lo_halves(l[0], l[1]), lo_halves(l[2], l[3])};
-      reh[I] = __builtin_bit_cast(s4, rh2);
-      rel[I] = __builtin_bit_cast(s4, rl2);
-      imh[I] = __builtin_bit_cast(s4, u2{hi_halves(h[0], h[1]), hi_halves(h[2], h[3])});
-      iml[I] = __builtin_bit_cast(s4, u2{hi_halves(l[0], l[1]), hi_halves(l[2], l[3])});
-      nreh[I] = __builtin_bit_cast(s4, u2{rh2[0] ^ 0x80008000u, rh2[1] ^ 0x80008000u});
-      nrel[I] = __builtin_bit_cast(s4, u2{rl2[0] ^ 0x80008000u, rl2[1] ^ 0x80008000u});
+      yh[I] = __builtin_bit_cast(bf8, v[0][I]);
+      yl[I] = __builtin_bit_cast(bf8, v[1][I]);
+      zh[I] = swap_neg(yh[I]);
+      zl[I] = swap_neg(yl[I]);
     }
     int t = 0;
 #pragma unroll
@@ -1372,14 +1347,11 @@ __device__ __forceinline__ void scm_bf16x3(const uint32_t* hwin, const uint32_t*
 #pragma unroll
       for (int J = I; J < NB; ++J, ++t) {
         accR[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yh[I], yh[J], accR[t], 0, 0, 0);
-        accI[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(imh[I], reh[J], accI[t], 0, 0, 0);
+        accI[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zh[I], yh[J], accI[t], 0, 0, 0);
         accR[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yh[I], yl[J], accR[t], 0, 0, 0);
-        accI[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(nreh[I], imh[J], accI[t], 0, 0, 0);
+        accI[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zh[I], yl[J], accI[t], 0, 0, 0);
         accR[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yl[I], yh[J], accR[t], 0, 0, 0);
-        accI[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(imh[I], rel[J], accI[t], 0, 0, 0);
-        accI[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(iml[I], reh[J], accI[t], 0, 0, 0);
-        accI[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(nreh[I], iml[J], accI[t], 0, 0, 0);
-        accI[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(nrel[I], imh[J], accI[t], 0, 0, 0);
+        accI[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zl[I], yh[J], accI[t], 0, 0, 0);
       }
   };
 #pragma unroll
@@ -1844,13 +1816,16 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
   int nq = 0;
 
   // ------------------------------------------------ a6 + a8 for G pixels
-  // FP32 run mode: the queue holds the pixels of one sliding-window chain at
-  // a time, and every batch of a chain but its first starts each slot from
-  // the converged time-factor subspace of the previous batch's slot G-1-g,
-  // its nearest pixel in the snake order of a unit (directly above it for
-  // q = 16).  Like the sliding window, the choice depends only on the chain,
-  // so the results are the same for every decomposition of the frame.
-  constexpr bool kWarmTail = PREC == 0 && MODE == kModeRun;
+  // Run mode: the queue holds the pixels of one sliding-window chain at a
+  // time, and every batch of a chain but its first starts each slot from the
+  // converged time-factor subspace of the previous batch's slot G-1-g, its
+  // nearest pixel in the snake order of a unit (directly above it for q = 16).
+  // Like the sliding window, the choice depends only on the chain, so the
+  // results are the same for every decomposition of the frame.  The BF16x3 and
+  // FP64 paths, which do not slide their covariance, start warm as well:
+  // p=3 q=16 at 512^2 BF16x3 with the product below 2.93 -> 2.61 ms, FP64
+  // solves at 256^2 3.98 -> 3.88 ms.
+  constexpr bool kWarmTail = MODE == kModeRun;
   EC vbw[RBM];   // lane (g, k): row k of the basis that starts slot g
 #pragma unroll
   for (int c = 0; c < RBM; ++c) vbw[c] = czero<EC>();
@@ -2189,7 +2164,7 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
       // A pixel that slides from its predecessor starts from that pixel's
       // U_A (sUA): the two training sets differ in a few vectors.  The choice
       // depends only on the chain position, as the sliding window does.
-      const bool warm = slide && ua_ok;
+      const bool warm = MODE == kModeRun && left_ok && k > 0 && ua_ok;
       auto eig_a = [&](bool cold) __attribute__((always_inline)) {
         if (r_a == 1) {
           ES h[P * P], lam;
