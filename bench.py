@@ -185,9 +185,11 @@ def _log(msg):
 
 def _roofs(plan, H, W, sec, prec):
     """Covariance work the kernel executes per second against the MFMA roof
-    of the arithmetic it runs on: FP32 MFMA for the plain path; for the
-    split-BF16 path the BF16 peak divided by its three products (the bf16x3
-    roof) and the BF16 peak itself (the stricter roof of a single product)."""
+    of the arithmetic it runs on: for the FP32 covariance the BF16 peak divided
+    by its six products of exact BF16 parts, and the FP32 MFMA peak beside it;
+    for the split-BF16 path the BF16 peak divided by its three products (the
+    bf16x3 roof) and the BF16 peak itself (the stricter roof of a single
+    product)."""
     pq = plan.p * plan.q
     vec, npx = executed_vectors(plan, H, W, slides_for(plan))
     tfl = vec * 4.0 * pq * (pq + 1) / sec / 1e12
@@ -196,7 +198,7 @@ def _roofs(plan, H, W, sec, prec):
     if prec == "bf16x3":
         out.update(frac_bf16x3_roof=tfl / (MFMA_BF16_PEAK_TFLOPS / 3.0), frac_bf16_k1_roof=tfl / MFMA_BF16_PEAK_TFLOPS)
     else:
-        out.update(frac_fp32_mfma_roof=tfl / MFMA_FP32_PEAK_TFLOPS)
+        out.update(frac_bf16x6_roof=tfl / (MFMA_BF16_PEAK_TFLOPS / 6.0), frac_fp32_mfma_roof=tfl / MFMA_FP32_PEAK_TFLOPS)
     return out
 
 
@@ -397,7 +399,7 @@ def form_large_q(kstap, torch, cpu=True):
                 solve = _timed(torch, lambda: kstap.lrkron(xd, eps=eps, with_B=False), 20)
                 row = dict(p=p, q=q, n=5, eps=eps, iterations=int(st[1]), eta=float(st[0]), us_total=full * 1e6,
                            us_solve=solve * 1e6,
-                           emit_b_GBps=q * q * 8 / max(full - solve, 1e-9) / 1e9)
+                           b_bytes_per_call_GBps=q * q * 8 / full / 1e9)
                 if cpu and q <= 1000:
                     t0 = time.perf_counter()
                     LQ.lr_kron_snapshots(X, eps=eps)
@@ -406,8 +408,8 @@ def form_large_q(kstap, torch, cpu=True):
                 _log(f"large q p={p} q={q} eps={eps:g}: {full * 1e6:.1f} us ({int(st[1])} iterations)")
     return dict(workload="one covariance from n=5 snapshots, rank-one A, B = I_q (Sec. 6.1 timing setting)",
                 rows=rows,
-                note="B-hat emission is bound by writing q^2 complex64 values; emit_b_GBps = q^2 * 8 bytes over "
-                     "(total - solve) time")
+                note="B-hat emission is bound by writing q^2 complex64 values; b_bytes_per_call_GBps = q^2 * 8 "
+                     "bytes over the whole call; the solve alone (no B-hat) keeps its Gram sums on one workgroup")
 
 
 def form_variants(kstap, torch):
@@ -625,8 +627,9 @@ def main():
     flops = vec * 4.0 * pq * (pq + 1)
     achieved = flops / (ms_per_step / 1e3) / 1e12
     dense = scm_flops_per_pixel(plan_kw["p"], plan_kw["q"], plan_kw["n"]) * valid_px / (ms_per_step / 1e3) / 1e12
-    # the split-BF16 path runs three BF16 products per FP32-class product
-    peak = MFMA_BF16_PEAK_TFLOPS / 3 if mixed else MFMA_FP32_PEAK_TFLOPS
+    # BF16 products per FP32-class product: three on the split-BF16 path, six
+    # of the exact three-part split on the plain path
+    peak = MFMA_BF16_PEAK_TFLOPS / (3 if mixed else 6)
     result = {
         "metric": "Kron-STAP output pixels/s on 1 MI355X (" +
                   ("split-BF16 covariance, FP64 solves" if mixed else "plain FP32 path") + ")",
@@ -654,6 +657,7 @@ def main():
             "peak": peak,
             "unit": "TFLOP/s",
             "frac": achieved / peak,
+            "frac_fp32_mfma": achieved / MFMA_FP32_PEAK_TFLOPS,
             "traffic": profiled_traffic(args.workload),   # HBM bytes per launch, rocprofv3 counters
             "credited": f"executed covariance work: {vec / valid_px:.3f} training vectors per valid pixel "
                         f"(sliding-window updates counted as the vectors they add and remove) x 4 pq (pq+1) "

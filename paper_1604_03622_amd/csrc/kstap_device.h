@@ -23,13 +23,14 @@
 //       time factor b = R^T conj(a) / ||a||^2 and the sums R conj(b).
 //       EIG_{r_a} (Eq. (17)): power iteration for r_a = 1, subspace
 //       iteration otherwise, warm-started from the previous iterate.
-//   a6  the final b = R^T conj(a) / ||a||^2 (Hermitian) is queued in
-//       registers; every 64/q' pixels (q' = q rounded up to 8, 16 or 32)
-//       one batched subspace iteration finds the top-r_b subspaces, q' lanes
-//       per pixel with group-local DPP reductions (CGS2, residual stop).
+//   a6  the final b = R^T conj(a) / ||a||^2 (Hermitian) is queued as slots
+//       in LDS; every 64/q' pixels (q' = q rounded up to 8, 16 or 32) one
+//       batched subspace iteration finds the top-r_b subspaces, q' lanes per
+//       pixel with group-local DPP reductions (CGS2, residual stop), the rank
+//       a compile-time constant (kstap_tail.h; tail_batch for the variants).
 //   a8  T = ||F_A X conj(F_B b_s)||^2 / (b_s^H F_B b_s) (Sec. 5, Eq. (25);
 //       Sec. 6.3, Eq. (26)); D = T > tau.
-// Wide pixels (p*q > 64): one 4-wave workgroup per pixel, see below.
+// Wide pixels (p*q > 64): one 8-wave workgroup per pixel, see below.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -1291,7 +1292,10 @@ __device__ __forceinline__ void split_store(const SplitAcc<P, Q>& acc, int n, fl
 // wavefront holds vectors 4g .. 4g + 3.
 //   Both tiles of v_mfma_f32_16x16x32_bf16 over the 16 vectors of the chunk:
 //   Re S on Y = (re, im) pairs, re_I re_J + im_I im_J; Im S with the row
-//   operand (im, -re), im_I re_J - re_I im_J.
+//   operand (im, -re), im_I re_J - re_I im_J.  36 MFMAs per chunk and three
+//   16-row blocks; Im S on single components through the 16 x 16 x 16 form
+//   took 54 and a half-word gather per operand (p = 3, q = 16, 1024 x 1024
+//   11.8 -> 10.3 ms with the warm starts of the solves).
 __device__ __forceinline__ bf8 swap_neg(bf8 y) {
   u4 w = __builtin_bit_cast(u4, y);
 #pragma unroll
