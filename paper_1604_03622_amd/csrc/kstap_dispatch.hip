@@ -32,6 +32,18 @@ __global__ void reset_counters(unsigned long long* c, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) c[i] = 0ull;
 }
 
+// A serving step's tables, read over the bus from mapped host memory, and its
+// zeroed queue counters.  Bound by one round trip to the host (every thread
+// reads one word): a copy-engine transfer of the same bytes is queued behind
+// the frame uploads in flight and held the step back until they had ended.
+constexpr int kTableThreads = 256, kTableGrid = 64;
+__global__ __launch_bounds__(kTableThreads) void load_tables(const uint64_t* __restrict__ src, uint64_t* __restrict__ dst,
+                                                             int64_t words, unsigned long long* c, int n) {
+  const int64_t stride = int64_t(gridDim.x) * kTableThreads;
+  for (int64_t i = int64_t(blockIdx.x) * kTableThreads + threadIdx.x; i < words; i += stride) dst[i] = src[i];
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < n; i += kTableThreads) c[i] = 0ull;
+}
 
 // all built kernels; a kernel class is an index into this table
 const std::vector<const Entry*>& table() {
@@ -115,6 +127,15 @@ const void* reset_kernel() { return reinterpret_cast<const void*>(&reset_counter
 
 int launch_reset(unsigned long long* counters, int n, hipStream_t stream) {
   hipLaunchKernelGGL(reset_counters, dim3(1), dim3(64), 0, stream, counters, n);
+  return hipGetLastError();
+}
+
+int launch_tables(const void* src, void* dst, size_t bytes, unsigned long long* counters, int n, hipStream_t stream) {
+  const int64_t words = int64_t((bytes + 7) / 8);
+  const int64_t grid = (words + kTableThreads - 1) / kTableThreads;
+  hipLaunchKernelGGL(load_tables, dim3(unsigned(grid < 1 ? 1 : grid > kTableGrid ? kTableGrid : grid)),
+                     dim3(kTableThreads), 0, stream, static_cast<const uint64_t*>(src), static_cast<uint64_t*>(dst), words,
+                     counters, n);
   return hipGetLastError();
 }
 

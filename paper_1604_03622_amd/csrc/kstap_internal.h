@@ -251,6 +251,9 @@ inline unsigned split_grid(int64_t n) {
 
 // Zeroes n device counters with a kernel (no memset node in graphs).
 int launch_reset(unsigned long long* counters, int n, hipStream_t stream);
+// Copies `bytes` (rounded up to 8) of mapped host memory to the device and
+// zeroes n counters, in one kernel.
+int launch_tables(const void* src, void* dst, size_t bytes, unsigned long long* counters, int n, hipStream_t stream);
 
 // Workgroups of class `cls` that one compute unit holds: the persistent grid is
 // this times the compute units (times a tuned multiple).

@@ -1,7 +1,7 @@
 // Scheduling core of the serving runtime (stap_server_*): an HBM arena,
 // admission of frames in arrival order while their buffers fit, fair-share
 // slicing of the active frames into steps, and a pipeline of up to two steps
-// in flight on one compute queue.
+// in flight, which the executor may run beside each other.
 //
 // The core holds no device code and makes no HIP call: every device action
 // goes through the Exec interface, so the same scheduler runs against the HIP
@@ -11,7 +11,7 @@
 // Invariants:
 //   * a frame's arena range is released only when no slice of it is in
 //     flight (after the steps holding its slices have completed, or after the
-//     executor has drained the compute queue following a failure);
+//     executor has drained its compute queues following a failure);
 //   * a frame record is deleted only by wait(), after it reached kDone or
 //     kFailed, and no in-flight step refers to it any more;
 //   * step slots are reused only after their step has completed, so the
@@ -373,7 +373,7 @@ class Scheduler {
     while (true) {
       admit_locked();
       poll_locked();
-      // retire completed steps, oldest first (one compute queue: in order)
+      // retire completed steps, oldest first
       bool progressed = false;
       while (true) {
         int oldest = -1;
@@ -417,7 +417,7 @@ class Scheduler {
       if (progressed) continue;
       const bool steps_busy = steps_[0].busy || steps_[1].busy;
       if (stop_ && pending_.empty() && active_.empty() && !steps_busy) break;
-      cv_work_.wait_for(lk, std::chrono::microseconds(steps_busy ? 50 : 200));
+      cv_work_.wait_for(lk, std::chrono::microseconds(active_.empty() ? 200 : 10));
     }
   }
 
