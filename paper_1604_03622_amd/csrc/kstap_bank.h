@@ -353,7 +353,7 @@ __device__ __forceinline__ void run_pixels_bank(const KParams& prm, int64_t firs
       EC ua[P];
 #pragma unroll
       for (int i = 0; i < P; ++i) ua[i] = warm ? sUA[i * RAM] : czero<EC>();
-      auto eig_a = [&](bool cold) __attribute__((always_inline)) {
+      auto eig_a = [&](bool cold, bool first) __attribute__((always_inline)) {
         EC Ah[P * P];
 #pragma unroll
         for (int i = 0; i < P; ++i)
@@ -361,14 +361,28 @@ __device__ __forceinline__ void run_pixels_bank(const KParams& prm, int64_t firs
           for (int j = 0; j < P; ++j)
             Ah[i * P + j] = cscale(cadd(cto<EC>(Ap[i * P + j]), cconj(cto<EC>(Ap[j * P + i]))), ES(0.5));
         if (r_a == 1) {
-          power_top<P, EC>([&](int i, int j) { return Ah[i * P + j]; }, ua, cold, 500, 2e-6);
-          ES lam = 0;
+          // The check of a start that power_top_h makes at its first step comes
+          // after the solve here, which leaves the rounding of every step, and
+          // with it the bins, as it was.
+          const auto Af = [&](int i, int j) { return Ah[i * P + j]; };
+          ES lam;
+          for (bool again = false;; again = true) {
+            power_top<P, EC>(Af, ua, cold && !again, 500, 2e-6);
+            ES tr = 0;
+            EC s[P];
+            lam = 0;
 #pragma unroll
-          for (int i = 0; i < P; ++i) {
-            EC s = czero<EC>();
+            for (int i = 0; i < P; ++i) {
+              s[i] = czero<EC>();
 #pragma unroll
-            for (int j = 0; j < P; ++j) s = cfma(Ah[i * P + j], ua[j], s);
-            lam += ua[i].x * s.x + ua[i].y * s.y;
+              for (int j = 0; j < P; ++j) s[i] = cfma(Ah[i * P + j], ua[j], s[i]);
+              lam += ua[i].x * s[i].x + ua[i].y * s[i].y;
+              tr += Ah[i * P + i].x;
+            }
+            if (again || stands_out(lam, tr)) break;
+            const ES inv = xrsqrt(xmax(start_anew<P, EC, ES>(Af, s, lam, tr, cold, first), tiny<ES>()));
+#pragma unroll
+            for (int i = 0; i < P; ++i) ua[i] = cscale(s[i], inv);
           }
           anorm2 = 0.f;
 #pragma unroll
@@ -401,7 +415,7 @@ __device__ __forceinline__ void run_pixels_bank(const KParams& prm, int64_t firs
         wave_sync();
         if constexpr (P <= 4) {
           uniform_subspace<RAM, P, EC>([&](int i, int j) { return Ah[i * P + j]; }, r_a, Vb, cold, 500,
-                                       2e-6);
+                                       2e-6, first ? 0.f : kMixOwn);
         } else {
           if (lane == 0) {
 #pragma unroll
@@ -417,7 +431,7 @@ __device__ __forceinline__ void run_pixels_bank(const KParams& prm, int64_t firs
 #pragma unroll
           for (int c = 0; c < RAM; ++c) va[c] = (!cold && lane < P) ? sUA[lane * RAM + c] : czero<EC>();
           wave_sync();   // sUA is rewritten below
-          group_subspace<RAM, 64, P, EC>(mrow, lane < P, r_a, va, sAh, cold, 500, 2e-6);
+          group_subspace<RAM, 64, P, EC>(mrow, lane < P, r_a, va, sAh, cold, 500, 2e-6, false, !cold, first ? 0.f : kMixOwn);
           // every lane gathers the whole basis from LDS
           if (lane < P) {
 #pragma unroll
@@ -477,7 +491,7 @@ __device__ __forceinline__ void run_pixels_bank(const KParams& prm, int64_t firs
       };
 
       sweep(false);
-      eig_a(!warm);
+      eig_a(!warm, true);
       iters = 1;
       double eta_prev = INFINITY;
       while (true) {
@@ -488,7 +502,7 @@ __device__ __forceinline__ void run_pixels_bank(const KParams& prm, int64_t firs
                           (prm.eps > 0.0 && iters >= prm.min_iter && fabs(e - eta_prev) <= prm.eps);
         if (stop) break;
         eta_prev = e;
-        eig_a(false);
+        eig_a(false, false);
         ++iters;
       }
       // bv now holds the final b = R^T conj(a) / ||a||^2

@@ -274,6 +274,56 @@ __device__ __forceinline__ void orth_cgs2(C (&w)[RM], int r, bool act) {
   }
 }
 
+// A solve that starts from another matrix's basis V stops once M V lies in the
+// span of V, and that holds for every invariant subspace: where the leading
+// directions of M are orthogonal to V (training sets with exact zeros: samples
+// or channels that are empty on one side of an edge), the iteration would keep
+// a subspace that is not the leading one, or none at all where M V = 0.  A
+// direction missing from V has at most the eigenvalue tr M - tr V^H M V (M is
+// positive semidefinite), so the first step checks that this is far below every
+// column's Rayleigh quotient, as it is for clutter of the plan's rank; where
+// that holds nothing changes.  Where it does not, the solve goes on from M V
+// with generic directions added at `mix` times each column's size: the next
+// residual sees a missing direction unless its eigenvalue lies within the
+// tolerance over `mix` of a kept one.  mix = 0 starts anew, from the generic
+// block: LR-Kron goes on from the result of its first EIG_{r_a}, so between two
+// nearly equal eigenvalues it has to be the larger one's and not the
+// neighbour's that comes out ahead when the steps are used up.  Its later ones
+// start from the pixel's own iterate, some 1e-2 to 1e-3 off, and mix no more.
+constexpr float kMixNeighbour = 1.f / 16.f, kMixOwn = 1e-3f;
+constexpr float kCaptured = 64.f;   // least Rayleigh quotient over the trace outside V
+// The check for lane groups whose rows lie as in group_subspace, w = M v;
+// `guard` is the same in all rows of a group.  Returns whether this lane's group
+// got another w.
+template <int RM, int QP, int D, typename C>
+__device__ __forceinline__ bool guard_start(const float2 (&mrow)[D], const C (&v)[RM], C (&w)[RM], int r, int k,
+                                            bool row_ok, bool guard, float mix) {
+  using S = decltype(C{}.x);
+  asm volatile("" : "+v"(k));   // nothing of this is hoisted out of the iteration
+  float diag = 0.f;
+#pragma unroll
+  for (int l = 0; l < D; ++l) diag = (l == k) ? mrow[l].x : diag;
+  const S tr = gsum<QP>(S(row_ok ? diag : 0.f));
+  S rest = tr, least = tr;
+#pragma unroll
+  for (int c = 0; c < RM; ++c) {
+    if (c >= r) continue;
+    const S t = gsum<QP>(row_ok ? v[c].x * w[c].x + v[c].y * w[c].y : S(0));
+    rest -= t;
+    least = t < least ? t : least;
+  }
+  const bool lost = guard && !(S(kCaptured) * rest <= least);
+  if (__ballot(lost) == 0) return false;
+#pragma unroll
+  for (int c = 0; c < RM; ++c) {
+    if (c >= r) continue;
+    const S t = gsum<QP>(row_ok ? v[c].x * w[c].x + v[c].y * w[c].y : S(0));
+    const C g = cto<C>(omega(k, c));
+    if (lost && row_ok) w[c] = mix > 0.f ? cadd(w[c], cscale(g, S(mix) * xmax(t, tr / S(D)))) : g;
+  }
+  return lost;
+}
+
 // Top-r invariant subspace of one Hermitian D x D matrix per lane group by
 // subspace iteration.  Lane k of a group holds row k of the matrix (mrow) and
 // row k of the orthonormal basis v (CGS2 orthonormalisation).  `cold` starts from M * Omega (Omega a
@@ -286,9 +336,11 @@ __device__ __forceinline__ void orth_cgs2(C (&w)[RM], int r, bool act) {
 // result is the one it would reach alone.  sV: LDS scratch of RM * D * (64 / QP) C
 // for this wavefront.  WAVE_LOCAL: the wavefront shares its workgroup with
 // others that run their own solves, so it synchronises only its own lanes.
+// `guard`: the start block is another matrix's basis (guard_start, with `mix`).
 template <int RM, int QP, int D, typename C, bool WAVE_LOCAL = false>
 __device__ __forceinline__ int group_subspace(const float2 (&mrow)[D], bool row_ok, int r, C (&v)[RM],
-                                              C* sV, bool cold, int max_steps, double tol, bool keep = false) {
+                                              C* sV, bool cold, int max_steps, double tol, bool keep = false,
+                                              bool guard = false, float mix = 0.f) {
   using S = decltype(C{}.x);
   constexpr int G = 64 / QP;
   const int lane = threadIdx.x & 63, g = lane / QP, k = lane % QP;   // lane within its wavefront
@@ -353,6 +405,7 @@ __device__ __forceinline__ int group_subspace(const float2 (&mrow)[D], bool row_
       wn = gsum<QP>(wn);
       conv = rn <= S(tol * tol) * wn;
     }
+    if (step == 0 && __ballot(guard)) conv = !guard_start<RM, QP, D, C>(mrow, v, w, r, k, row_ok, guard, mix) && conv;
     orth_cgs2<RM, QP, C>(w, r, row_ok);
     // a group keeps the first basis computed from a converged one and is
     // frozen from then on, so its result does not depend on its neighbours
@@ -372,9 +425,11 @@ __device__ __forceinline__ int group_subspace(const float2 (&mrow)[D], bool row_
 // computed identically by every lane with no cross-lane traffic: the
 // subspace iteration, CGS2 and stopping rule of group_subspace, on a matrix
 // read through M(i, j).  V[c][i] is entry i of basis column c; `cold` starts
-// from M * Omega, otherwise V is the warm start.  Returns the step count.
+// from M * Omega, otherwise V is the warm start, checked as by guard_start with
+// `mix`.  Returns the step count.
 template <int RM, int P, typename C, typename MF>
-__device__ __forceinline__ int uniform_subspace(MF M, int r, C (&V)[RM][P], bool cold, int max_steps, double tol) {
+__device__ __forceinline__ int uniform_subspace(MF M, int r, C (&V)[RM][P], bool cold, int max_steps, double tol,
+                                                float mix) {
   using S = decltype(C{}.x);
   if (cold) {
 #pragma unroll
@@ -427,6 +482,33 @@ __device__ __forceinline__ int uniform_subspace(MF M, int r, C (&V)[RM][P], bool
       }
       conv = rn <= S(tol * tol) * wn;
     }
+    if (step == 0 && !cold) {   // as guard_start
+      S tr = 0, t[RM];
+#pragma unroll
+      for (int i = 0; i < P; ++i) tr += M(i, i).x;
+      S rest = tr, least = tr;
+#pragma unroll
+      for (int c = 0; c < RM; ++c) {
+        t[c] = 0;
+        if (c >= r) continue;
+#pragma unroll
+        for (int i = 0; i < P; ++i) t[c] += V[c][i].x * Wm[c][i].x + V[c][i].y * Wm[c][i].y;
+        rest -= t[c];
+        least = t[c] < least ? t[c] : least;
+      }
+      if (!(S(kCaptured) * rest <= least)) {
+        conv = false;
+#pragma unroll
+        for (int c = 0; c < RM; ++c)
+#pragma unroll
+          for (int i = 0; i < P; ++i) {
+            int ii = i;
+            asm volatile("" : "+v"(ii));   // computed here, not hoisted into every solve
+            const C g = (c < r) ? cto<C>(omega(ii, c)) : czero<C>();
+            Wm[c][i] = mix > 0.f ? cadd(Wm[c][i], cscale(g, S(mix) * xmax(t[c], tr / S(P)))) : g;
+          }
+      }
+    }
     // CGS2 on the columns of W
 #pragma unroll
     for (int c = 0; c < RM; ++c) {
@@ -469,6 +551,44 @@ __device__ __forceinline__ int uniform_subspace(MF M, int r, C (&V)[RM][P], bool
     if (done || step >= max_steps) break;
   }
   return step;
+}
+
+// The check of guard_start for one vector, at the first step of a solve: lam =
+// u^H M u stands out from the trace of M, so no direction outside u has a larger
+// eigenvalue.  Where it does not, the step's result w gives way to the cold start
+// (a column of M) if u was a neighbour's (`first`: a pixel's first solve), and
+// takes a generic direction: a cold start may itself be an eigenvector of a
+// smaller eigenvalue.
+template <typename S>
+__device__ __forceinline__ bool stands_out(S lam, S tr) {
+  return S(4) * (tr - lam) <= lam;
+}
+// the generic direction, as constants (computed, it would be hoisted into every
+// solve)
+__device__ constexpr float kGeneric[kMaxP][2] = {{0.80f, -0.60f}, {-0.25f, 0.86f}, {0.66f, 0.88f}, {-0.77f, -0.22f},
+                                                 {0.91f, 0.27f}, {-0.45f, 0.60f}, {0.31f, -1.06f}, {-0.88f, 0.47f}};
+// w, or column j (read through M(i, j)) of the largest diagonal entry, plus the
+// generic direction; returns the squared norm
+template <int P, typename C, typename S, typename MF>
+__device__ __forceinline__ S start_anew(MF M, C (&w)[P], S lam, S tr, bool cold, bool first) {
+  if (first && !cold) {
+    S db = M(0, 0).x;
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+      const bool up = j == 0 || M(j, j).x > db;
+      db = up ? M(j, j).x : db;
+#pragma unroll
+      for (int i = 0; i < P; ++i) w[i] = up ? M(i, j) : w[i];
+    }
+  }
+  const S mix = S(first ? kMixNeighbour : kMixOwn) * xmax(lam, tr / S(P));
+  S wn = 0;
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    w[i] = cadd(w[i], cscale(cto<C>(make_float2(kGeneric[i][0], kGeneric[i][1])), mix));
+    wn += cabs2(w[i]);
+  }
+  return wn;
 }
 
 // Dominant eigenvector of a Hermitian P x P matrix, the same for every lane;
@@ -532,8 +652,8 @@ __host__ __device__ constexpr int hoff(int i, int j) { return P + 2 * (i * P - i
 // the general complex product); *lam receives u^H M u of the last iterate
 // tested, whose error is the square of the stopping residual.
 template <int P, typename C, typename S>
-__device__ __forceinline__ void power_top_h(const S (&h)[P * P], C (&u)[P], bool cold, int max_steps, double tol,
-                                            S* lam_out) {
+__device__ __forceinline__ void power_top_h(const S (&h)[P * P], C (&u)[P], bool cold, bool first, int max_steps,
+                                            double tol, S* lam_out) {
   if (cold) {   // the column of the largest diagonal entry
     int jb = 0;
     S db = h[0];
@@ -585,6 +705,20 @@ __device__ __forceinline__ void power_top_h(const S (&h)[P * P], C (&u)[P], bool
     }
 #pragma unroll
     for (int i = 0; i < P; ++i) rn += cabs2(csub(w[i], cscale(u[i], lam)));
+    if (step == 0) {
+      S tr = 0;
+#pragma unroll
+      for (int i = 0; i < P; ++i) tr += h[i];
+      if (!stands_out(lam, tr))
+        rn = wn = start_anew<P, C, S>(
+            [&](int i, int j) __attribute__((always_inline)) {
+              C m;
+              m.x = i == j ? h[i] : i < j ? h[hoff<P>(i, j)] : h[hoff<P>(j, i)];
+              m.y = i == j ? S(0) : i < j ? h[hoff<P>(i, j) + 1] : -h[hoff<P>(j, i) + 1];
+              return m;
+            },
+            w, lam, tr, cold, first);
+    }
     if (!(wn > S(0))) break;
     const S inv = xrsqrt(xmax(wn, tiny<S>()));
 #pragma unroll
@@ -1441,7 +1575,8 @@ __device__ __forceinline__ void tail_batch(const KParams& prm, const float2 (&Bq
   // the loop exits on the step cap, so a group never runs unbounded
   constexpr int kTailSteps = sizeof(ES) == 8 ? 4000 : 200;
   if (r_b > 0)
-    group_subspace<RBM, QP, Q, EC, WAVE_LOCAL>(Bq, rok && flag == 0, r_b, vb, scratch, true, kTailSteps, tol, keep);
+    group_subspace<RBM, QP, Q, EC, WAVE_LOCAL>(Bq, rok && flag == 0, r_b, vb, scratch, true, kTailSteps, tol, keep,
+                                               keep, kMixNeighbour);
   vb_ok = rok && flag == 0;
   // statistic
   int pr, pc;
@@ -2169,12 +2304,13 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
       // U_A (sUA): the two training sets differ in a few vectors.  The choice
       // depends only on the chain position, as the sliding window does.
       const bool warm = MODE == kModeRun && left_ok && k > 0 && ua_ok;
-      auto eig_a = [&](bool cold) __attribute__((always_inline)) {
+      // `first`: the first of this pixel.
+      auto eig_a = [&](bool cold, bool first) __attribute__((always_inline)) {
         if (r_a == 1) {
           ES h[P * P], lam;
 #pragma unroll
           for (int e = 0; e < P * P; ++e) h[e] = ES(Ap[e]);
-          power_top_h<P, EC, ES>(h, ua, cold, 500, PREC ? 1e-12 : 2e-6, &lam);
+          power_top_h<P, EC, ES>(h, ua, cold, first, 500, PREC ? 1e-12 : 2e-6, &lam);
 #pragma unroll
           for (int i = 0; i < P; ++i) {
             A[i] = float(lam * cabs2(ua[i]));
@@ -2212,7 +2348,7 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
         wave_sync();
         if constexpr (P <= 4) {
           uniform_subspace<RAM, P, EC>([&](int i, int j) { return Ah[i * P + j]; }, r_a, Vb, cold, 500,
-                                       PREC ? 1e-12 : 2e-6);
+                                       PREC ? 1e-12 : 2e-6, first ? 0.f : kMixOwn);
         } else {
           if (lane == 0) {
 #pragma unroll
@@ -2228,7 +2364,8 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
 #pragma unroll
           for (int c = 0; c < RAM; ++c) va[c] = (!cold && lane < P) ? sUA[lane * RAM + c] : czero<EC>();
           wave_sync();   // sUA is rewritten below
-          group_subspace<RAM, 64, P, EC>(mrow, lane < P, r_a, va, sAh, cold, 500, PREC ? 1e-12 : 2e-6);
+          group_subspace<RAM, 64, P, EC>(mrow, lane < P, r_a, va, sAh, cold, 500, PREC ? 1e-12 : 2e-6, false, !cold,
+                                         first ? 0.f : kMixOwn);
           // every lane gathers the whole basis from LDS
           if (lane < P) {
 #pragma unroll
@@ -2305,7 +2442,7 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
           eta_prev = e;
         }
         half_ap();
-        eig_a(k == 0 && !warm);
+        eig_a(k == 0 && !warm, k == 0);
         iters = k + 1;
       }
       // bv now holds the final b = R^T conj(a) / ||a||^2
@@ -2941,7 +3078,7 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
     if (!zero && !bad) {
       // EIG_{r_a} of A' = R conj(b) / ||b||^2 on wave 0 (the sums over the
       // wavefronts are in red), which writes A to sA
-      auto eig_a = [&](bool cold) __attribute__((always_inline)) {
+      auto eig_a = [&](bool cold, bool first) __attribute__((always_inline)) {
         if (wave != 0) return;
         const float mine = total(lane <= P * P ? lane : P * P);
         const float binv = 1.f / __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine), P * P));
@@ -2950,7 +3087,7 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
 #pragma unroll
           for (int e = 0; e < P * P; ++e)
             h[e] = ES(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine), e)) * binv);
-          power_top_h<P, EC, ES>(h, ua, cold, 500, PREC == 1 ? 1e-12 : 2e-6, &lam);
+          power_top_h<P, EC, ES>(h, ua, cold, first, 500, PREC == 1 ? 1e-12 : 2e-6, &lam);
           if (lane == 0) {
 #pragma unroll
             for (int i = 0; i < P; ++i) {
@@ -3000,7 +3137,8 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
 #pragma unroll
             for (int c = 0; c < R; ++c)
               va[c] = !rowk ? czero<EC>() : cold ? cto<EC>(omega(lane, c)) : sUA[lane * RAM + c];
-            rows_subspace<R, 8, P, EC, true>(mrow, lane >> 3, lane & 7, va, scr, 500, 2e-6, !cold);
+            rows_subspace<R, 8, P, EC, true>(mrow, lane >> 3, lane & 7, va, scr, 500, 2e-6, !cold, !cold,
+                                             first ? 0.f : kMixOwn);
             if (rowk) {
 #pragma unroll
               for (int c = 0; c < R; ++c) sUA[lane * RAM + c] = va[c];
@@ -3033,7 +3171,8 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
           EC va[RAM];
 #pragma unroll
           for (int c = 0; c < RAM; ++c) va[c] = (!cold && rowk) ? sUA[lane * RAM + c] : czero<EC>();
-          group_subspace<RAM, 64, P, EC, true>(mrow, rowk, r_a, va, reinterpret_cast<EC*>(scr), cold, 500, 1e-12);
+          group_subspace<RAM, 64, P, EC, true>(mrow, rowk, r_a, va, reinterpret_cast<EC*>(scr), cold, 500, 1e-12, false, !cold,
+                                               first ? 0.f : kMixOwn);
           lane_sync();
           if (rowk) {
 #pragma unroll
@@ -3123,7 +3262,7 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
           if (stop) break;
           eta_prev = e;
         }
-        eig_a(k == 0 && !warm);
+        eig_a(k == 0 && !warm, k == 0);
         iters = k + 1;
         block_sync();   // publishes sA; red and redd are free again
         load_a();

@@ -69,11 +69,12 @@ constexpr size_t tail_scratch_bytes = size_t(G) * (sizeof(C) * R * D + 16);
 
 // group_subspace for exactly R columns and zero rows: the top-R invariant
 // subspace of one Hermitian D x D matrix per lane group.  v enters as the
-// start block (tested at the first step if `tested`) and leaves as the basis.
-// Same iteration, stopping rule and freezing.
+// start block (tested at the first step if `tested`) and leaves as the basis;
+// `guard` where it is another matrix's (guard_start, with `mix`).  Same iteration,
+// stopping rule and freezing.
 template <int R, int QP, int D, typename C, bool WAVE_LOCAL>
 __device__ __forceinline__ void rows_subspace(const float2 (&mrow)[D], int g, int k, C (&v)[R], char* scratch,
-                                              int max_steps, double tol, bool tested = false) {
+                                              int max_steps, double tol, bool tested, bool guard, float mix) {
   using S = decltype(C{}.x);
   C* const sV = reinterpret_cast<C*>(scratch + g * (sizeof(C) * R * D + 16));
   bool done = false;
@@ -153,6 +154,7 @@ __device__ __forceinline__ void rows_subspace(const float2 (&mrow)[D], int g, in
       wn = gsum<QP>(wn);
       conv = rn <= S(tol * tol) * wn;
     }
+    if (step == 0 && __ballot(guard)) conv = !guard_start<R, QP, D, C>(mrow, v, w, R, k, k < D, guard, mix) && conv;
     orth_rows<R, QP, C>(w);
     // a group keeps the first basis computed from a converged one and is
     // frozen from then on, so its result does not depend on its neighbours
@@ -211,7 +213,8 @@ __device__ __forceinline__ void tail_rows(const KParams& prm, float2 (&Bq)[Q], i
     // FP64 solves iterate until converged where the r_b-th and next eigenvalues
     // of B lie close together (a ratio of 0.99 takes ~1 500 steps to 1e-10);
     // the loop exits on the step cap, so a group never runs unbounded
-    rows_subspace<R, QP, Q, EC, WAVE_LOCAL>(Bq, lane / QP, tk, v, scratch, sizeof(ES) == 8 ? 4000 : 200, tol);
+    rows_subspace<R, QP, Q, EC, WAVE_LOCAL>(Bq, lane / QP, tk, v, scratch, sizeof(ES) == 8 ? 4000 : 200, tol, false,
+                                            keep, kMixNeighbour);
 #pragma unroll
     for (int c = 0; c < R; ++c) vb[c] = v[c];
   }
