@@ -152,9 +152,11 @@ __global__ __launch_bounds__(kSolveThreads) void lrk_gram(const float2* __restri
 // over pair subsets; wave 0 adds them, takes EIG_{r_a} (parallel Jacobi, one
 // lane per matrix entry) and the stop decision.
 //
-// For many samples the Gram sums of nparts workgroups (lrk_gram) are read from
-// `part` instead.
-template <int P>
+// For many samples (PARTS) the Gram sums of nparts workgroups (lrk_gram) are
+// read from `part` instead: a kernel of its own, because with both routes in one
+// the small solves took 0.5 to 1.4 % longer (p, q, n = 2, 25, 4 20.26 -> 20.55
+// us; 8, 100, 8 173.4 -> 174.7).
+template <int P, bool PARTS>
 __global__ __launch_bounds__(kSolveThreads) void lrk_solve(const float2* __restrict__ X, LrkParams prm,
                                                            const double* __restrict__ part, int nparts) {
   constexpr int p = P;
@@ -210,8 +212,8 @@ __global__ __launch_bounds__(kSolveThreads) void lrk_solve(const float2* __restr
       pre[j] = (u < np && k < len) ? X[int64_t(u) * q + k0 + k] : make_float2(0.f, 0.f);
     }
   };
-  const int nch = part ? 0 : (q + chunk - 1) / chunk;
-  if (part) {
+  const int nch = PARTS ? 0 : (q + chunk - 1) / chunk;
+  if constexpr (PARTS) {
 #pragma unroll
     for (int j = 0; j < kMaxEnt; ++j) {
       if (j >= ne) continue;
@@ -548,15 +550,16 @@ int launch_lrkron(const float2* X, const LrkParams& prm, hipStream_t stream) {
     part = reinterpret_cast<double*>(prm.B);
     hipLaunchKernelGGL(lrk_gram, dim3(nparts), dim3(kSolveThreads), 0, stream, X, np, prm.q, span, part);
   }
+  auto solve = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); };
   switch (prm.p) {
-    case 1: hipLaunchKernelGGL(lrk_solve<1>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
-    case 2: hipLaunchKernelGGL(lrk_solve<2>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
-    case 3: hipLaunchKernelGGL(lrk_solve<3>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
-    case 4: hipLaunchKernelGGL(lrk_solve<4>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
-    case 5: hipLaunchKernelGGL(lrk_solve<5>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
-    case 6: hipLaunchKernelGGL(lrk_solve<6>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
-    case 7: hipLaunchKernelGGL(lrk_solve<7>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
-    default: hipLaunchKernelGGL(lrk_solve<8>, dim3(1), dim3(kSolveThreads), 0, stream, X, prm, part, nparts); break;
+    case 1: part ? solve(lrk_solve<1, true>) : solve(lrk_solve<1, false>); break;
+    case 2: part ? solve(lrk_solve<2, true>) : solve(lrk_solve<2, false>); break;
+    case 3: part ? solve(lrk_solve<3, true>) : solve(lrk_solve<3, false>); break;
+    case 4: part ? solve(lrk_solve<4, true>) : solve(lrk_solve<4, false>); break;
+    case 5: part ? solve(lrk_solve<5, true>) : solve(lrk_solve<5, false>); break;
+    case 6: part ? solve(lrk_solve<6, true>) : solve(lrk_solve<6, false>); break;
+    case 7: part ? solve(lrk_solve<7, true>) : solve(lrk_solve<7, false>); break;
+    default: part ? solve(lrk_solve<8, true>) : solve(lrk_solve<8, false>); break;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !prm.B) return e;
