@@ -368,9 +368,10 @@ stap_status stap_sinr_loss(const stap_true_cov* cov, const stap_filter_set* filt
  * workgroup of a persistent kernel pops work items from a device counter until
  * the queue is empty.  pix_per_item = 0 takes, per kernel class, the tuned
  * entry of the tuning cache for the current device (else 16 positions and a
- * grid that fills the compute units once); pix_per_item > 0 applies to every class.  Results are bitwise equal to
- * stap_run on each tile alone.  The frames and outputs named by the tiles must
- * stay valid while the batch is launched.  Must be called with the device that
+ * grid of compute units x 8, or as many workgroups as these hold if that is
+ * more); pix_per_item > 0 applies to every class.  Results are bitwise equal
+ * to stap_run on each tile alone.  The frames and outputs named by the tiles
+ * must stay valid while the batch is launched.  Must be called with the device that
  * will run the batch current.  Tiles whose plan has a statistic variant
  * (classical filter, Doppler bank, several passes) are refused with
  * UNSUPPORTED (those run through stap_run_ex).
@@ -392,7 +393,7 @@ stap_status stap_batch_launch(stap_batch_t* batch, void* hip_stream);
 
 /* Autotuner: for every kernel class of the batch, alone, times (synchronously,
  * on hip_stream, with direct launches) work items of {16, 32, 64, 128}
- * positions and persistent grids of {1, 2, 4} x the workgroups that fill the compute units
+ * positions and persistent grids of {1, 2, 4} x (compute units x 8)
  * workgroups, keeps each class's fastest, rebuilds the graph, and records the
  * choices in the tuning cache (stap_tune_record) keyed by (device
  * architecture, p, q, r_b bound, precision).  best_ppb / best_grid_mult

@@ -29,7 +29,7 @@ struct BatchClass {
   int cls = -1;                  // kernel class
   std::vector<int32_t> order;    // tiles of this class, longest first
   int ppb = 16;                  // work-item size (tiled-order positions, a multiple of the chain)
-  int grid_mult = 1;             // persistent grid = compute units x workgroups per unit x grid_mult
+  int grid_mult = 1;             // persistent grid = compute units x 8 x grid_mult (persistent_grid)
 };
 
 int device_cus() {
@@ -230,7 +230,7 @@ stap_status batch_build(stap_batch_s* b) {
     void* args[] = {&descs, &order, &prefix, &nt, &ppb, &counter};
     hipKernelNodeParams np{};
     np.func = const_cast<void*>(kstap::persistent_kernel(c.cls));
-    np.gridDim = dim3(cus * kstap::persistent_wgs(c.cls) * c.grid_mult);
+    np.gridDim = dim3(kstap::persistent_grid(c.cls, cus, c.grid_mult));
     np.blockDim = dim3(64);
     np.sharedMemBytes = 0;
     np.kernelParams = args;
@@ -265,7 +265,7 @@ stap_status batch_launch_direct(stap_batch_s* b, hipStream_t s, bool splits = tr
     const BatchClass& c = b->classes[i];
     le = kstap::launch_persistent(c.cls, b->d_descs, b->d_order + b->order_base[i], b->d_prefix + b->prefix_base[i],
                                   int(c.order.size()), c.ppb, b->d_counters + i * kstap::kQueues,
-                                  cus * kstap::persistent_wgs(c.cls) * c.grid_mult, s);
+                                  kstap::persistent_grid(c.cls, cus, c.grid_mult), s);
   }
   if (le != hipSuccess) return fail(STAP_ERR_DEVICE, "batch launch: %s", hipGetErrorString(hipError_t(le)));
   return STAP_OK;
@@ -839,7 +839,7 @@ stap_status stap_batch_create(const stap_tile* tiles, int32_t ntiles, int32_t pi
     }
   }
   // work-item size and grid per class: as given, else the tuned entry of the
-  // class for this device, else 16 positions and a grid that fills the CUs once
+  // class for this device, else 16 positions and one grid
   const std::string arch = kstap::tune::device_arch();
   for (BatchClass& c : b->classes) {
     std::stable_sort(c.order.begin(), c.order.end(), [&](int32_t a, int32_t z) { return cost[a] > cost[z]; });
@@ -912,7 +912,7 @@ stap_status stap_batch_tune(stap_batch_t* batch, void* hip_stream, int32_t* best
     return fail(STAP_ERR_DEVICE, "event create failed");
   }
   // per class: work items of 16..128 positions (multiples of the chain) x
-  // persistent grids of 1, 2, 4 x (CUs x workgroups per CU), the class alone
+  // persistent grids of 1, 2, 4 x (CUs x 8) workgroups, the class alone
   const int ppbs[] = {16, 32, 64, 128};
   const int mults[] = {1, 2, 4};
   stap_status st = batch_launch_direct(batch, s, true, int(batch->classes.size()));   // the splits only

@@ -2575,6 +2575,12 @@ __global__ __launch_bounds__(64, (kWavesPerSimd<P, Q, RBM, PREC, VAR == kPlain &
 // device counters until every queue is empty (kQueues queues, see kstap_internal.h).  Items are numbered tile after
 // tile in the order of `order` (longest tiles first); prefix[j] is the first item of order[j] (prefix[nt] = total).
 template <int P, int Q, int RBM, int PREC>
+constexpr int resident_wgs() {   // a compute unit's share of registers and LDS (160 KB, 16 bytes beside the carve-out)
+  const int waves = 4 * kWavesPerSimd<P, Q, RBM, PREC, true>;
+  const int lds = int(size_t(160 * 1024) / (Lds<P, Q, RBM, PREC>::bytes + 16));
+  return waves < lds ? waves : lds;
+}
+template <int P, int Q, int RBM, int PREC>
 __global__ __launch_bounds__(64, (kWavesPerSimd<P, Q, RBM, PREC, true>)) void kstap_persistent(const KParams* __restrict__ descs,
                                                           const int32_t* __restrict__ order,
                                                           const int64_t* __restrict__ prefix, int nt,

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "kstap_internal.h"
@@ -113,7 +114,10 @@ const void* persistent_kernel(int cls) {
   return table()[cls]->persist_fn;
 }
 
-int persistent_wgs(int cls) { return cls < 0 || cls >= int(table().size()) ? 8 : table()[cls]->wgs; }
+int persistent_grid(int cls, int cus, int mult) {
+  const int held = cls < 0 || cls >= int(table().size()) ? 0 : table()[cls]->wgs;
+  return cus * std::max(8 * mult, held);
+}
 
 int launch_split(const float2* x, uint32_t* xs, int64_t n, hipStream_t stream) {
   if (n <= 0) return hipSuccess;

@@ -255,9 +255,10 @@ int launch_reset(unsigned long long* counters, int n, hipStream_t stream);
 // zeroes n counters, in one kernel.
 int launch_tables(const void* src, void* dst, size_t bytes, unsigned long long* counters, int n, hipStream_t stream);
 
-// Workgroups of class `cls` that one compute unit holds: the persistent grid is
-// this times the compute units (times a tuned multiple).
-int persistent_wgs(int cls);
+// Workgroups of a persistent launch of class `cls`: mult x 8 per compute unit, the
+// unit that tuned entries are saved in, and no fewer than a unit holds (12 of the
+// FP32 q = 8 classes; 512 x 512, n = 64 877 -> 715 us as a frame).
+int persistent_grid(int cls, int cus, int mult);
 
 // Host handles of the persistent kernel of class `cls` (arguments: descs,
 // order, prefix, nt, ppb, counter) and of the counter-reset kernel

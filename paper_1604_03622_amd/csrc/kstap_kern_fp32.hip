@@ -5,7 +5,7 @@ namespace kstap {
 
 #define KSTAP_ENTRY(P, Q, R, X) \
   {P, Q, R, X, X == 1, &launch_one<P, Q, R, X>, &launch_persist<P, Q, R, X>, \
-   reinterpret_cast<const void*>(&kstap_persistent<P, Q, R, X>), 4 * kWavesPerSimd<P, Q, R, X, true>}
+   reinterpret_cast<const void*>(&kstap_persistent<P, Q, R, X>), resident_wgs<P, Q, R, X>()}
 // the table is a local static of a host function (a namespace-scope const
 // array would also be emitted, unresolvable, for the device)
 const Entry* entries_fp32(int* count) {

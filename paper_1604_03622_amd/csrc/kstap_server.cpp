@@ -208,7 +208,7 @@ class HipExec : public ks::Exec {
       le = kstap::launch_persistent(L.first, reinterpret_cast<const kstap::KParams*>(d),
                                     reinterpret_cast<const int32_t*>(d + o_order) + L.second.first,
                                     reinterpret_cast<const int64_t*>(d + o_prefix) + L.second.second, nt, ppb,
-                                    s.d_ctr + c * kstap::kQueues, cus * kstap::persistent_wgs(L.first), s.stream);
+                                    s.d_ctr + c * kstap::kQueues, kstap::persistent_grid(L.first, cus, 1), s.stream);
     }
     if (le == hipSuccess) le = hipEventRecord(s.ev, s.stream);
     return check(hipError_t(le));

@@ -13,7 +13,7 @@ namespace tune {
 
 struct Entry {
   int ppb = 16;         // work-item size in tiled-order positions (a multiple of the sliding-window chain)
-  int grid_mult = 1;    // persistent grid = workgroups that fill the compute units x grid_mult
+  int grid_mult = 1;    // persistent grid = compute units x 8 x grid_mult (at least what the units hold)
   double ms = 0.0;      // time of the class alone when it was tuned
 };
 
