@@ -157,6 +157,17 @@ inline void plan_slices(const std::vector<Frame*>& ready, int64_t step_positions
     if (take[i] > 0) out->push_back({ready[i], ready[i]->cursor, ready[i]->cursor + take[i]});
 }
 
+// Microseconds that the worker sleeps before it looks again: 1/32 of the time
+// since something last changed, so that a short step is seen within a few per
+// cent of its length and a long one does not keep a CPU and the submitters' lock
+// busy; never more than 50 us while steps run, 200 us else.  Six frames in 5.2
+// ms: 10 us throughout, 1/32 and 1/16 5.20, 5.20 and 5.24 ms, 50 us 0.14 ms more.
+inline int poll_wait_us(bool active, bool steps_busy, double idle_s) {
+  const int most = steps_busy ? 50 : 200;
+  if (!active) return most;
+  return std::max(10, std::min(most, int(std::min(idle_s, 1.0) * 1e6 / 32)));
+}
+
 struct Config {
   size_t budget = 0;
   int max_inflight = 16;
@@ -308,9 +319,12 @@ class Scheduler {
     }
   }
 
-  void poll_locked() {
+  // whether a frame's state changed
+  bool poll_locked() {
+    bool changed = false;
     const std::vector<Frame*> act = active_;   // finish_locked edits active_
     for (Frame* f : act) {
+      const int was = f->state;
       if (f->state == kUploading) {
         const Exec::Poll p = exec_->upload_state(f);
         if (p == Exec::kReady) f->state = kComputing;
@@ -320,7 +334,9 @@ class Scheduler {
         if (p == Exec::kReady) finish_locked(f, STAP_OK, std::string());
         else if (p == Exec::kError) finish_locked(f, STAP_ERR_DEVICE, exec_->error());
       }
+      changed = changed || f->state != was;
     }
+    return changed;
   }
 
   // A completed step: its slices are done; frames whose last slice it held
@@ -370,9 +386,11 @@ class Scheduler {
       fatal_ = exec_->error();
     }
     std::vector<Slice> slices;
+    double changed = now_s();
     while (true) {
+      const size_t waiting = pending_.size();
       admit_locked();
-      poll_locked();
+      if (poll_locked() || pending_.size() != waiting) changed = now_s();
       // retire completed steps, oldest first
       bool progressed = false;
       while (true) {
@@ -412,12 +430,16 @@ class Scheduler {
         const bool ok = exec_->launch(free_slot, slices);
         lk.lock();
         if (!ok) recover_locked(lk, free_slot);
+        changed = now_s();
         continue;
       }
-      if (progressed) continue;
+      if (progressed) {
+        changed = now_s();
+        continue;
+      }
       const bool steps_busy = steps_[0].busy || steps_[1].busy;
       if (stop_ && pending_.empty() && active_.empty() && !steps_busy) break;
-      cv_work_.wait_for(lk, std::chrono::microseconds(active_.empty() ? 200 : 10));
+      cv_work_.wait_for(lk, std::chrono::microseconds(poll_wait_us(!active_.empty(), steps_busy, now_s() - changed)));
     }
   }
 

@@ -11,8 +11,8 @@
 // bus in a small kernel, not behind the uploads on a copy engine, and results
 // leave on a stream of their own.  Six frames of 10 to 77 MB (3.4 ms of
 // uploads, 3.1 ms of kernels): 5.70 ms with one copy and one compute stream,
-// 5.26 ms so, 5.12 ms with the worker looking every 10 us while frames are in
-// flight (50 or 200 us before).  A step's tables (parameter blocks, work order,
+// 5.26 ms so, 5.12 ms with the worker looking soon after a change
+// (poll_wait_us).  A step's tables (parameter blocks, work order,
 // prefix sums, queue counters) live in one of two slots, so the next step is
 // enqueued while the previous one runs and the GPU does not wait for the host
 // between steps.
