@@ -38,9 +38,7 @@ struct BankLds {
   static constexpr size_t oOff = oQidx + sizeof(int64_t) * G;             // uint32[kMaxN + kOffPad]
   static constexpr size_t oDelta = oOff + sizeof(uint32_t) * (kMaxN + kOffPad);   // uint32[3][2][kMaxDelta + 8]
   static constexpr size_t oQflag = oDelta + sizeof(uint32_t) * 6 * (kMaxDelta + 8);   // int[G]
-  static constexpr size_t oQit = oQflag + sizeof(int) * G;                // int[G]
-  static constexpr size_t oQeta = oQit + sizeof(int) * G;                 // float[G]
-  static constexpr size_t bytes = ((oQeta + sizeof(float) * G) + 15) / 16 * 16;
+  static constexpr size_t bytes = ((oQflag + sizeof(int) * G) + 15) / 16 * 16;
 };
 
 // The whole per-pixel pass of run mode for `count` positions starting at
@@ -72,8 +70,6 @@ __device__ __forceinline__ void run_pixels_bank(const KParams& prm, int64_t firs
   EC* const tail_scratch = reinterpret_cast<EC*>(sBT);
   int64_t* const sQidx = reinterpret_cast<int64_t*>(lds + L::oQidx);             //   pixel index
   int* const sQflag = reinterpret_cast<int*>(lds + L::oQflag);                   //   0 ok, 1 zero, 2 non-finite
-  float* const sQeta = reinterpret_cast<float*>(lds + L::oQeta);
-  int* const sQit = reinterpret_cast<int*>(lds + L::oQit);
 
   const int lane = threadIdx.x;
   const int n = prm.n;
@@ -135,8 +131,7 @@ __device__ __forceinline__ void run_pixels_bank(const KParams& prm, int64_t firs
   auto tail = [&](int nfill) __attribute__((always_inline)) {
     const bool keep = bchain == qchain && vbw_ok;
     bool ok;
-    tail_batch<P, Q, RBM, kModeRun, EC, false, true>(prm, Bq, tg, nfill, sQflag, sQidx, sQeta, sQit, sQUA, tail_scratch,
-                                                2e-6, vbw, keep, ok);
+    tail_batch<P, Q, RBM, EC, false>(prm, Bq, tg, nfill, sQflag, sQidx, sQUA, tail_scratch, 2e-6, vbw, keep, ok);
     bchain = qchain;
     const int src = (G - 1 - tg) * QP + tk;
 #pragma unroll
@@ -272,7 +267,6 @@ __device__ __forceinline__ void run_pixels_bank(const KParams& prm, int64_t firs
       }
     }
 
-    float eta = 0.f;
     int iters = 0;
     const bool zero = !(normR2 > 0.0);
     const bool bad = !isfinite(normR2);
@@ -497,7 +491,6 @@ __device__ __forceinline__ void run_pixels_bank(const KParams& prm, int64_t firs
       while (true) {
         sweep(true);
         const double e = sqrt(resid / normR2);
-        eta = float(e);
         const bool stop = iters >= prm.max_iter ||
                           (prm.eps > 0.0 && iters >= prm.min_iter && fabs(e - eta_prev) <= prm.eps);
         if (stop) break;
@@ -538,8 +531,6 @@ __device__ __forceinline__ void run_pixels_bank(const KParams& prm, int64_t firs
     if (lane == 0) {
       sQidx[nq] = idx;
       sQflag[nq] = bad ? 2 : (zero ? 1 : 0);
-      sQeta[nq] = eta;
-      sQit[nq] = iters;
     }
     if (lane < P * RAM) sQUA[nq][lane] = (zero || bad) ? czero<EC>() : sUA[lane];
     wave_sync();

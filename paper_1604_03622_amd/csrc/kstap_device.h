@@ -1542,20 +1542,21 @@ __device__ __forceinline__ void write_outside(const KParams& prm, int64_t idx) {
 }
 
 // ------------------------------------------------ a6 + a8, batched
-// Top-r_b time subspace, projected test vector and statistic for up to
+// The tail of the statistic variants in run mode (the plain statistic and the
+// probe take tail_rows): top-r_b time subspace, projected test vector and statistic for up to
 // 64 / QP queued pixels of one wavefront: lane group `slot` (QP lanes) serves
 // queue slot `slot`, whose lane k holds row k of the pixel's Hermitian time
 // factor in Bq; slots >= nfill are empty.  Per slot the queue holds the pixel
-// index, a flag (0 ok, 1 zero covariance, 2 non-finite), eta, the iteration
-// count and U_A (p x RAM).  Writes T (and D, or the probe outputs).
+// index, a flag (0 ok, 1 zero covariance, 2 non-finite) and U_A (p x RAM).
+// Writes T, D and the variants' outputs.
 // WAVE_LOCAL: other wavefronts of the workgroup run their own tails.
 // vb: this lane's row of its slot's basis; on entry the warm start of the
 // slots whose lanes set `keep` (the others start cold), on return the basis.
-template <int P, int Q, int RBM, int MODE, typename EC, bool WAVE_LOCAL, bool VAR>
+template <int P, int Q, int RBM, typename EC, bool WAVE_LOCAL>
 __device__ __forceinline__ void tail_batch(const KParams& prm, const float2 (&Bq)[Q], int slot, int nfill,
-                                           const int* sQflag, const int64_t* sQidx, const float* sQeta,
-                                           const int* sQit, const EC (*sQUA)[P * ((P < kMaxRA) ? P : kMaxRA)],
-                                           EC* scratch, double tol, EC (&vb)[RBM], bool keep, bool& vb_ok) {
+                                           const int* sQflag, const int64_t* sQidx,
+                                           const EC (*sQUA)[P * ((P < kMaxRA) ? P : kMaxRA)], EC* scratch, double tol,
+                                           EC (&vb)[RBM], bool keep, bool& vb_ok) {
   using ES = decltype(EC{}.x);
   constexpr int RAM = (P < kMaxRA) ? P : kMaxRA;
   constexpr int QP = Groups<Q>::QP;
@@ -1579,14 +1580,7 @@ __device__ __forceinline__ void tail_batch(const KParams& prm, const float2 (&Bq
                                                keep, kMixNeighbour);
   vb_ok = rok && flag == 0;
   // statistic
-  int pr, pc;
-  if (MODE == kModeRun) {
-    pr = int(pidx / W);
-    pc = int(pidx - int64_t(pr) * W);
-  } else {
-    pr = prm.pix[2 * pidx];
-    pc = prm.pix[2 * pidx + 1];
-  }
+  const int pr = int(pidx / W), pc = int(pidx - int64_t(pr) * W);
   const bool use = rok && flag == 0;
   // this lane's sample of every channel of the test snapshot
   const float2* xt = prm.x + (int64_t(pr) * W + pc) * Q;
@@ -1623,11 +1617,11 @@ __device__ __forceinline__ void tail_batch(const KParams& prm, const float2 (&Bq
   // Temporal steering: the plan's b_s, or each bin of a Doppler bank
   // b_m[k] = exp(2 pi j ((m k) mod M) / M); the statistic is the largest over
   // the bank, the bin its first maximiser.
-  const int nbank = VAR ? prm.nbank : 0;
+  const int nbank = prm.nbank;
   const int nbins = nbank > 0 ? nbank : 1;
-  const int K = VAR ? prm.passes : 1, PP = K > 1 ? P / K : P;
-  const int filter = VAR ? prm.filter : 0;
-  float* const Eout = VAR ? prm.E : nullptr;
+  const int K = prm.passes, PP = K > 1 ? P / K : P;
+  const int filter = prm.filter;
+  float* const Eout = prm.E;
   float T = 0.f, Ebest = 0.f;
   int best = 0;
   ES ez[P];   // per-channel energy |z_i|^2 / (b^H F_B b) at the best bin (passes > 1)
@@ -1725,45 +1719,27 @@ __device__ __forceinline__ void tail_batch(const KParams& prm, const float2 (&Bq
   if (flag == 2) T = NAN;
   if (slot_ok && tk == 0) {
     prm.T[pidx] = T;
-    if (MODE == kModeRun) {
-      if (prm.D) prm.D[pidx] = (T > prm.tau) ? 1 : 0;
-      const int64_t hw = int64_t(H) * W;
-      if (Eout) Eout[pidx] = flag == 2 ? NAN : (flag == 1 ? 0.f : Ebest);
-      if (VAR && prm.bin) prm.bin[pidx] = uint8_t(flag == 0 ? best : 0);
-      // pass k's image: the energy of its channels of z (passes > 1)
-      if (K > 1 && (prm.Tpass || prm.C)) {
-        ES t0 = 0;
+    if (prm.D) prm.D[pidx] = (T > prm.tau) ? 1 : 0;
+    const int64_t hw = int64_t(H) * W;
+    if (Eout) Eout[pidx] = flag == 2 ? NAN : (flag == 1 ? 0.f : Ebest);
+    if (prm.bin) prm.bin[pidx] = uint8_t(flag == 0 ? best : 0);
+    // pass k's image: the energy of its channels of z (passes > 1)
+    if (K > 1 && (prm.Tpass || prm.C)) {
+      ES t0 = 0;
+#pragma unroll
+      for (int i = 0; i < P; ++i)
+        if (i < PP) t0 += ez[i];
+#pragma unroll
+      for (int k = 0; k < P; ++k) {
+        if (k >= K) continue;
+        ES ts = 0;
 #pragma unroll
         for (int i = 0; i < P; ++i)
-          if (i < PP) t0 += ez[i];
-#pragma unroll
-        for (int k = 0; k < P; ++k) {
-          if (k >= K) continue;
-          ES ts = 0;
-#pragma unroll
-          for (int i = 0; i < P; ++i)
-            if (i / PP == k) ts += ez[i];
-          if (prm.Tpass) prm.Tpass[k * hw + pidx] = flag == 2 ? NAN : (flag == 1 ? 0.f : float(ts));
-          if (prm.C && k > 0)
-            prm.C[(k - 1) * hw + pidx] = flag == 2 ? NAN : (flag == 1 ? 0.f : float(sqrt(ts) - sqrt(t0)));
-        }
+          if (i / PP == k) ts += ez[i];
+        if (prm.Tpass) prm.Tpass[k * hw + pidx] = flag == 2 ? NAN : (flag == 1 ? 0.f : float(ts));
+        if (prm.C && k > 0)
+          prm.C[(k - 1) * hw + pidx] = flag == 2 ? NAN : (flag == 1 ? 0.f : float(sqrt(ts) - sqrt(t0)));
       }
-    }
-    if (MODE == kModeProbe) {
-      if (prm.eta) prm.eta[pidx] = sQeta[slot];
-      if (prm.iters) prm.iters[pidx] = sQit[slot];
-    }
-  }
-  if (MODE == kModeProbe && slot_ok) {
-    if (prm.UA && tk < P) {
-#pragma unroll
-      for (int c = 0; c < RAM; ++c)
-        if (c < r_a) prm.UA[(pidx * P + tk) * r_a + c] = (flag != 0) ? cz() : tof(sQUA[slot][tk * RAM + c]);
-    }
-    if (prm.UB && tk < Q) {
-#pragma unroll
-      for (int c = 0; c < RBM; ++c)
-        if (c < r_b) prm.UB[(pidx * Q + tk) * r_b + c] = (flag != 0) ? cz() : tof(vb[c]);
     }
   }
   lds_sync<WAVE_LOCAL>();
@@ -1980,8 +1956,8 @@ __device__ __forceinline__ void run_pixels(const KParams& prm, int64_t first, in
       queue_row<P, Q>(sQB + (lanev / QP) * NS, k < Q ? k : 0, Bq);   // empty slots: whatever is there, unused
     }
     if constexpr (VAR) {
-      tail_batch<P, Q, RBM, MODE, EC, false, true>(prm, Bq, tg, nfill, sQflag, sQidx, sQeta, sQit, sQUA, tail_scratch,
-                                                   PREC ? 1e-10 : 2e-6, vbw, keep, ok);
+      tail_batch<P, Q, RBM, EC, false>(prm, Bq, tg, nfill, sQflag, sQidx, sQUA, tail_scratch, PREC ? 1e-10 : 2e-6, vbw,
+                                       keep, ok);
     } else {
       with_rank<RBM>(r_b, [&](auto rank) __attribute__((always_inline)) {
         tail_rows<P, Q, RBM, decltype(rank)::value, MODE, EC, false>(
@@ -2772,8 +2748,8 @@ __device__ __forceinline__ void run_pixels_wide(const KParams& prm, int64_t firs
       for (int c = 0; c < RBM; ++c) vb[c] = czero<EC>();
       bool vb_ok;
       if constexpr (VAR) {
-        tail_batch<P, Q, RBM, MODE, EC, true, true>(prm, Bq, slot, nfill, sQflag, sQidx, sQeta, sQit, sQUA,
-                                                    reinterpret_cast<EC*>(scr), PREC ? 1e-10 : 2e-6, vb, false, vb_ok);
+        tail_batch<P, Q, RBM, EC, true>(prm, Bq, slot, nfill, sQflag, sQidx, sQUA, reinterpret_cast<EC*>(scr),
+                                        PREC ? 1e-10 : 2e-6, vb, false, vb_ok);
       } else {
         with_rank<RBM>(r_b, [&](auto rank) __attribute__((always_inline)) {
           tail_rows<P, Q, RBM, decltype(rank)::value, MODE, EC, true>(prm, Bq, wave * G, nfill, sQflag, sQidx, sQeta, sQit,
