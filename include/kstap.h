@@ -56,8 +56,8 @@ typedef enum {
 
 typedef enum {
   STAP_PREC_FP32 = 0,   /* covariance of FP32 samples in three exact BF16 parts on MFMA with FP32
-                           accumulation (FP32 MFMA for p q > 48 and the Doppler bank), everything
-                           else FP32 (eta terms FP64) */
+                           accumulation (FP32 MFMA for 48 < p q <= 64 and for the Doppler bank of
+                           p q <= 64), everything else FP32 (eta terms FP64) */
   STAP_PREC_BF16X3 = 1, /* covariance as three BF16 MFMA products (hi*hi + hi*lo + lo*hi) with
                            FP32 accumulation; eigensolves and normalisation in FP64 */
   STAP_PREC_FP32_FP64 = 2 /* covariance as for FP32 but as full sums (no sliding-window update),

@@ -9,6 +9,9 @@
 // keeps the arithmetic its results were first computed with: FP32 MFMA
 // covariance and sweeps of LR-Kron over all of R in LDS (6.9 ms on that frame
 // against 4.9 ms).  The batched tail, and with it the bank loop, is shared.
+// This holds for the narrow FP32 classes (p q <= 64) alone: a bank in the other
+// precisions or on the wide kernels shares the arithmetic of the plain statistic,
+// and bins of theirs that tie within its rounding may move with it.
 #pragma once
 
 namespace kstap {

@@ -290,6 +290,10 @@ __device__ __forceinline__ void orth_cgs2(C (&w)[RM], int r, bool act) {
 // nearly equal eigenvalues it has to be the larger one's and not the
 // neighbour's that comes out ahead when the steps are used up.  Its later ones
 // start from the pixel's own iterate, some 1e-2 to 1e-3 off, and mix no more.
+//   Measured with and without the check (results the same bit for bit): 64 x 64,
+// q = 8 92.1 / 90.8 us; 2048 x 2048, q = 16 22.70 / 22.52 ms; a batch of 12 tiles
+// 4.85 / 4.77 ms; two passes of p = 6, q = 16 at 256 x 256 6.76 / 6.66 ms; noise
+// alone at 512 x 512, where every start is mixed, 38.0 / 37.5 ms.
 constexpr float kMixNeighbour = 1.f / 16.f, kMixOwn = 1e-3f;
 constexpr float kCaptured = 64.f;   // least Rayleigh quotient over the trace outside V
 // The check for lane groups whose rows lie as in group_subspace, w = M v;
@@ -2507,10 +2511,12 @@ namespace kstap {
 namespace {
 
 // Wavefronts per SIMD that the run-mode kernels are compiled for.  The p = 3,
-// q = 8 FP32 kernel needs 172 registers on its own and nothing spills at the
-// 168 of three: 512 x 512, n = 64 877 -> 715 us.  p = 3, q = 16 needs 220: at
-// 168 it spills some 60 accesses a pixel and takes the 1024 x 1024 frame 7.9 ms
-// instead of 5.7.
+// q = 8 FP32 kernel needs 172 registers on its own and spills one or two (outside
+// its loops) at the 168 of three: 512 x 512, n = 64 874 -> 726 us.  p = 2, q = 8
+// needs 151 and runs three a SIMD either way (471 us).  p = 3, q = 8 with r_b > 4
+// needs 218: 960 us with two, 993 with three.  p = 3, q = 16 needs 224: at 168 it
+// spills some 60 accesses a pixel and takes the 1024 x 1024 frame 7.9 ms instead
+// of 5.7.
 template <int P, int Q, int RBM, int PREC, bool PLAIN>
 constexpr int kWavesPerSimd = (PLAIN && PREC == 0 && P <= 3 && Q == 8 && RBM == 4) ? 3 : 2;
 

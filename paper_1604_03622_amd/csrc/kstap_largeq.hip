@@ -46,9 +46,6 @@ constexpr size_t kOffPt = kOffPm + sizeof(dc) * kSolveThreads;
 constexpr size_t kRegion = kOffPt + sizeof(double) * kSolveThreads;
 static_assert(sizeof(float2) * (kStageMax + kLrkMaxRows) <= kRegion, "staged chunk fits the shared region");
 
-// P: channels, a compile-time constant so that the p x p matrices of the
-// iteration live in registers.
-//
 // Entry e of the upper triangle of an np x np matrix, row-major: (u, v), u <= v.
 __device__ __forceinline__ void tri_entry(int e, int np, int* u, int* v) {
   int r = 0;
@@ -151,6 +148,9 @@ __global__ __launch_bounds__(kSolveThreads) void lrk_gram(const float2* __restri
 // partial sums of M = sum T_(m,m') G_mm' and tb = Re sum tr(T_(m,m') T_(m',m))
 // over pair subsets; wave 0 adds them, takes EIG_{r_a} (parallel Jacobi, one
 // lane per matrix entry) and the stop decision.
+//
+// P: channels, a compile-time constant so that the p x p matrices of the
+// iteration live in registers.
 //
 // For many samples (PARTS) the Gram sums of nparts workgroups (lrk_gram) are
 // read from `part` instead: a kernel of its own, because with both routes in one
@@ -536,11 +536,15 @@ __global__ __launch_bounds__(256) void lrk_emit_b(const float2* __restrict__ X, 
 int launch_lrkron(const float2* X, const LrkParams& prm, hipStream_t stream) {
   if (prm.n * prm.p > kLrkMaxRows || prm.p > kLrkMaxP || prm.p < 1 || prm.q < 1) return hipErrorInvalidValue;
   // Many workgroups for the Gram sums where one would take most of the time and
-  // B-hat's memory, written last, holds their partial sums.  One workgroup
-  // against many, p, q, n: 3, 256, 5 47.1 / 44.4 us; 3, 512, 5 48.7 / 38.8;
-  // 3, 2500, 5 121 / 51; 6, 256, 5 108 / 96; 6, 1250, 5 200 / 101; 1, 4000, 64
-  // 1 778 / 294; but 2, 260, 3 (7 020 entries x samples) 22.7 / 23.7: there the
-  // extra launch costs more than it saves.
+  // B-hat's memory, written last, holds their partial sums (without B-hat there
+  // is no such memory, and the one workgroup takes longer than the call with it:
+  // p = 3, q = 2500 108 / 60 us).  One workgroup against many, p, q, n: 3, 256, 5
+  // 46.6 / 43.9 us; 3, 512, 5 48.7 / 38.8; 3, 2500, 5 121 / 51; 6, 256, 5 108 /
+  // 96; 6, 1250, 5 200 / 101; 1, 4000, 64 1 778 / 294; but 2, 260, 3 (7 020
+  // entries x samples) 22.5 / 23.2 and 2, 300, 3 (8 100) 22.6 / 23.2: there the
+  // extra launch costs more than it saves.  In between the many gain 0.4 to 2.3
+  // us: 2, 256, 5 (16 640) 25.6 / 25.3, 3, 256, 4 (23 040) 42.5 / 41.2, 3, 340,
+  // 4 (30 600) 44.1 / 41.9; the line was drawn below the first large gain.
   const int np = prm.n * prm.p, nent = np * (np + 1) / 2 + np;
   const int span = kGramChunk * ((prm.q + kGramChunk * kGramMaxBlocks - 1) / (kGramChunk * kGramMaxBlocks));
   const int nparts = (prm.q + span - 1) / span;
